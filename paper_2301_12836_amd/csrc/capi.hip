@@ -542,8 +542,7 @@ int ls_setup(const ls_grid* grid, const double C0[36], double rho0, const double
 
     const size_t n = (size_t)c->ncell;
     const size_t fe = 3 * n * (size_t)c->max_rhs;  // field elements of a batch
-    const size_t oct = c->green_half ? (size_t)(c->L1 / 2 + 1) * c->L2 * c->L3
-                                     : (size_t)(c->L1 / 2 + 1) * (c->L2 / 2 + 1) * (c->L3 / 2 + 1);
+    const size_t oct = green_pitch(c->L1) * (c->green_half ? (size_t)c->L2 * c->L3 : (size_t)(c->L2 / 2 + 1) * (c->L3 / 2 + 1));
     int rc = LS_OK;
     auto A = [&](void** p, size_t bytes) {
         if (rc == LS_OK) rc = dalloc(c, p, bytes);

@@ -63,6 +63,17 @@ __host__ __device__ __forceinline__ long long zrow_offset(int y, int zbs, int L1
     return ((long long)y << zbs) * L1;
 }
 
+// Elements between the six entries of one (k_z, k_y) row of the k-space Green's table: L1/2 + 1 rounded up to whole
+// 64-byte lines of FP32 values.  Each entry's k_x values are contiguous, so the lanes of a z-pass wavefront (adjacent
+// columns) read whole lines.
+__host__ __device__ __forceinline__ int green_pitch(int L1) { return (L1 / 2 + 8) / 8 * 8; }
+// element of entry e at k_x = x of row `row` (k_z, k_y): FP64 [row][6][pitch]; FP32 interleaves entries in pairs,
+// [row][3][pitch][2], so that both precisions are read with 16-byte loads
+template <typename T>
+__host__ __device__ __forceinline__ long long green_index(long long row, int e, int x, int pitch) {
+    return sizeof(T) == 8 ? (row * 6 + e) * pitch + x : ((row * 3 + e / 2) * pitch + x) * 2 + (e & 1);
+}
+
 // ------------------------------------------------------------------------------------------
 // right-hand sides of one launch
 
@@ -200,8 +211,8 @@ struct Ctx {
     // else 21
     int contrast_k = 21;
 
-    // k-space Green's tables per frequency: octant [L3/2+1][L2/2+1][L1/2+1][6] (half-space
-    // [L3][L2][L1/2+1][6] when green_half), already scaled by 1/(L1 L2 L3) so the inverse FFT needs no
+    // k-space Green's tables per frequency: octant, rows [L3/2+1][L2/2+1] of green_index layout (half-space: rows
+    // [L3][L2] when green_half), already scaled by 1/(L1 L2 L3) so the inverse FFT needs no
     // normalisation
     std::vector<z128*> ghat;
     std::vector<z128*> greal;     // LS_GREEN_ANISO: h^3 G at the offsets of one octant, [N3][N2][N1][6] per frequency

@@ -17,6 +17,30 @@
 
 namespace ls {
 
+// Bounds-checked view of `bytes` (< 2^32) bytes at a block-uniform address, as a buffer resource: loads past the end
+// return zero and stores past the end are dropped by the hardware, so a line's unused elements need no branches.
+// Byte offsets are 32 bit; loads and stores are non-temporal.
+template <typename T>
+struct Buffer {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Buffer(void* base, unsigned bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00027000)) {}
+    __device__ __forceinline__ cpx<T> load_nt(unsigned off) const {
+        if constexpr (sizeof(T) == 8)
+            return __builtin_bit_cast(cpx<T>, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 2));
+        else
+            return __builtin_bit_cast(cpx<T>, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 2));
+    }
+    __device__ __forceinline__ void store_nt(unsigned off, cpx<T> v) const {
+        if constexpr (sizeof(T) == 8)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), r, (int)off, 0, 2);
+        else
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, (int)off, 0, 2);
+    }
+    typedef unsigned U4 __attribute__((ext_vector_type(4)));
+    typedef unsigned U2 __attribute__((ext_vector_type(2)));
+};
+
 // cos(2 pi m / 32) for m = 0..8 (first quadrant); the rest by symmetry
 constexpr double kCos32[9] = {1.0,
                                                   0.98078528040323044912618223613424,
@@ -83,6 +107,44 @@ __device__ __forceinline__ void reg_dft(cpx<T>* v) {
     }
 }
 
+// The DFT of reg_dft with callbacks: in(j) gives element j, out(k, X_k) takes the results.  For N = 16 scheduling
+// fences separate the eight length-4 DFTs, so that only about N values are live at any point (without them the
+// scheduler interleaves all of them, which costs the z pass the registers of its second wave).
+template <int SIGN, int N, typename T, bool HALF, typename In, typename Out>
+__device__ __forceinline__ void reg_dft_io(In in, Out out) {
+    if constexpr (N <= 8) {
+        cpx<T> w[N];
+#pragma unroll
+        for (int j = 0; j < (HALF ? N / 2 : N); ++j) w[j] = in(j);
+        reg_dft<SIGN, N, T, HALF>(w);
+#pragma unroll
+        for (int k = 0; k < N; ++k) out(k, w[k]);
+    } else {
+        constexpr int A = 4, B = N / A;   // n = a + A b, k = k2 + B k1
+        cpx<T> tmp[N];
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            cpx<T> w[B];
+#pragma unroll
+            for (int b = 0; b < (HALF ? B / 2 : B); ++b) w[b] = in(a + A * b);
+            reg_dft<SIGN, B, T, HALF>(w);
+#pragma unroll
+            for (int k2 = 0; k2 < B; ++k2) tmp[a * B + k2] = (a * k2 == 0) ? w[k2] : w[k2] * unit_root<SIGN, N, T>(a * k2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) {
+            cpx<T> w[A];
+#pragma unroll
+            for (int a = 0; a < A; ++a) w[a] = tmp[a * B + k2];
+            SmallDft<SIGN, A, T>::run(w);
+#pragma unroll
+            for (int k1 = 0; k1 < A; ++k1) out(k2 + B * k1, w[k1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
 // cos(2 pi m / 24) for m = 0..6 (first quadrant); with unit_root24 the roots of unity of orders 3, 6, 12, 24
 constexpr double kCos24[7] = {1.0,
                               0.96592582628906828674974319972890,
@@ -141,6 +203,64 @@ __device__ __forceinline__ void reg_dft3(cpx<T>* v) {
             for (int k1 = 0; k1 < 3; ++k1) v[k2 + B * k1] = w[k1];
         }
     }
+}
+
+// DFT of odd length P with sign SIGN, natural order in and out: X_j and X_{P-j} are the sum and the difference of
+// v_0 + sum_k cos(2 pi j k / P) (v_k + v_{P-k}) and SIGN i sum_k sin(2 pi j k / P) (v_k - v_{P-k}), k <= P/2.
+// cos and sin of 2 pi m / P for m = 0..P/2
+template <int P>
+struct OddRoots;
+template <>
+struct OddRoots<5> {
+    static constexpr double c[3] = {1.0, 0.30901699437494742410229341718282, -0.80901699437494742410229341718282};
+    static constexpr double s[3] = {0.0, 0.95105651629515357211643933337938, 0.58778525229247312916870595463907};
+};
+template <>
+struct OddRoots<7> {
+    static constexpr double c[4] = {1.0, 0.62348980185873353052500488400424, -0.22252093395631440428890256449679,
+                                    -0.90096886790241912623610231950745};
+    static constexpr double s[4] = {0.0, 0.78183148246802980870844452667406, 0.97492791218182360701813168299393,
+                                    0.43388373911755812047576833284836};
+};
+template <int SIGN, int P, typename T>
+__device__ __forceinline__ void odd_dft(cpx<T>* v) {
+    constexpr int K = P / 2;
+    using R = OddRoots<P>;
+    cpx<T> t[K + 1], d[K + 1];
+#pragma unroll
+    for (int k = 1; k <= K; ++k) {
+        t[k] = v[k] + v[P - k];
+        d[k] = v[k] - v[P - k];
+    }
+    const cpx<T> v0 = v[0];
+#pragma unroll
+    for (int k = 1; k <= K; ++k) v[0] = v[0] + t[k];
+#pragma unroll
+    for (int j = 1; j <= K; ++j) {
+        cpx<T> m = v0, n = {T(0), T(0)};
+#pragma unroll
+        for (int k = 1; k <= K; ++k) {
+            const int a = (j * k) % P;
+            const T c = T(R::c[a <= K ? a : P - a]), s = T(a <= K ? R::s[a] : -R::s[P - a]);
+            m = m + c * t[k];
+            n = n + s * d[k];
+        }
+        n = mul_si<SIGN>(n);
+        v[j] = m + n;
+        v[P - j] = m - n;
+    }
+}
+
+// In-register DFT of length N = 2..16 (the second stage of an asymmetric four-step) with sign SIGN, natural order
+// in and out
+template <int SIGN, int N, typename T>
+__device__ __forceinline__ void reg_dft_any(cpx<T>* v) {
+    if constexpr ((N & (N - 1)) == 0)
+        reg_dft<SIGN, N, T>(v);
+    else if constexpr (N == 3 || N == 6 || N == 12)
+        reg_dft3<SIGN, N, T>(v);
+    else
+        odd_dft<SIGN, N, T>(v);
 }
 
 template <int L>
@@ -228,19 +348,6 @@ __device__ __forceinline__ int spectral_index(int q, int i) {
     return (q + F::N1 * s) + F::N2 * k1;
 }
 
-// Paired four-step: N1 = 2 N2 threads per line, N2 values each (the same natural layout: thread p holds
-// x[p + N1 j]).  It serves the z pass where the square split would hold 32 values of each of three
-// components per thread (512 = 32 x 16 instead of 16 x 32).  After the first DFT and the transpose,
-// thread p = 2 k2 + h holds the N2 inputs n1 = 2 m + h of the length-N1 DFT for k2 and transforms them;
-// the radix-2 step that joins the two halves exchanges values with the partner thread p ^ 1, TX lanes
-// away in the same wavefront.  Spectral layout: thread p holds X[k2 + N2 (i + N2 h)] at v[i].  Selections
-// between the halves are made per real component (sel): a select of whole structs kept them in scratch.
-template <int L>
-struct FourStepPair {
-    static constexpr int N2 = (L == 512) ? 16 : (L == 128) ? 8 : (L == 32) ? 4 : 0;
-    static constexpr int N1 = 2 * N2;
-    static_assert(N2 > 0 && N1 * N2 == L, "unsupported length");
-};
 template <typename T>
 __device__ __forceinline__ cpx<T> sel(bool h, cpx<T> a, cpx<T> b) { return {h ? a.x : b.x, h ? a.y : b.y}; }
 // The 32-bit value of lane (this lane XOR M) of the wavefront.  M = 1 and M = 8 stay inside a 16-lane row and
@@ -270,107 +377,29 @@ __device__ __forceinline__ double xor_lane(double x) {
 // the value of lane (this lane XOR M); every lane of the wavefront must take part
 template <int M, typename T>
 __device__ __forceinline__ cpx<T> lane_xor(cpx<T> a) { return {xor_lane<M>(a.x), xor_lane<M>(a.y)}; }
-// the partner's value in the paired split of length L: the DPP exchange from length 384 up; at length 128
-// (FP64 at 64^3) the crossbar measured faster (0.216 against 0.225-0.232 ms)
-template <int M, int L, typename T>
-__device__ __forceinline__ cpx<T> pair_partner(cpx<T> a) {
-    if constexpr (L >= 384)
-        return lane_xor<M>(a);
-    else
-        return {__shfl_xor(a.x, M), __shfl_xor(a.y, M)};
+// The radix-2 step between the halves of a pair (thread p = 2 k2 + h, partner TX lanes away) of a line of length L: the
+// forward twiddles W_L^{i B} of half 1, then sum (half 0) or difference (half 1); the inverse undoes it.  Half 0
+// multiplies by the table's entry 0, 1, and the sign enters as a factor, so neither half selects between results
+// (the selects cost the z pass at 384 150 spilled registers in FP64).
+template <int SIGN, int M, typename T>
+__device__ __forceinline__ cpx<T> pair_forward(cpx<T> v, int ib, int h, T sgn, const cpx<T>* __restrict__ tw) {
+    if (ib > 0) v = v * tw_at<SIGN>(tw, h * ib);
+    const cpx<T> o = lane_xor<M>(v);
+    return {o.x + sgn * v.x, o.y + sgn * v.y};
 }
-template <typename T, int L, int TX, int SIGN, bool HALF = false>
-__device__ __forceinline__ void fsp_forward(cpx<T>* v, cpx<T>* lds, const cpx<T>* __restrict__ tw, int t, int p) {
-    using F = FourStepPair<L>;
-    static_assert(2 * TX <= 64, "partner lanes must share a wavefront");
-    reg_dft<SIGN, F::N2, T, HALF>(v);
-#pragma unroll
-    for (int k2 = 1; k2 < F::N2; ++k2) v[k2] = v[k2] * tw_at<SIGN>(tw, p * k2);
-#pragma unroll
-    for (int k2 = 0; k2 < F::N2; ++k2) lds[(k2 * F::N1 + p) * TX + t] = v[k2];
-    __syncthreads();
-    const int k2 = p >> 1;
-    const bool h = p & 1;
-#pragma unroll
-    for (int m = 0; m < F::N2; ++m) v[m] = lds[(k2 * F::N1 + 2 * m + (int)h) * TX + t];
-    __syncthreads();
-    reg_dft<SIGN, F::N2, T>(v);
-#pragma unroll
-    for (int i = 0; i < F::N2; ++i) {
-        cpx<T> mine = v[i];
-        if (i > 0) mine = sel(h, mine * tw_at<SIGN>(tw, i * F::N2), mine);
-        const cpx<T> other = pair_partner<TX, L>(mine);
-        v[i] = sel(h, other - mine, mine + other);
-    }
+template <int SIGN, int M, typename T>
+__device__ __forceinline__ cpx<T> pair_backward(cpx<T> v, int ib, int h, T sgn, const cpx<T>* __restrict__ tw) {
+    const cpx<T> o = lane_xor<M>(v);
+    const cpx<T> d = {o.x + sgn * v.x, o.y + sgn * v.y};
+    return ib > 0 ? d * tw_at<SIGN>(tw, h * ib) : d;
 }
-template <typename T, int L, int TX, int SIGN>
-__device__ __forceinline__ void fsp_backward(cpx<T>* v, cpx<T>* lds, const cpx<T>* __restrict__ tw, int t, int p) {
-    using F = FourStepPair<L>;
-    const int k2 = p >> 1;
-    const bool h = p & 1;
-#pragma unroll
-    for (int i = 0; i < F::N2; ++i) {
-        const cpx<T> mine = v[i];
-        const cpx<T> other = pair_partner<TX, L>(mine);
-        const cpx<T> d = other - mine;
-        const cpx<T> dw = (i > 0) ? d * tw_at<SIGN>(tw, i * F::N2) : d;
-        v[i] = sel(h, dw, mine + other);
-    }
-    reg_dft<SIGN, F::N2, T>(v);
-#pragma unroll
-    for (int m = 0; m < F::N2; ++m) {
-        const int n1 = 2 * m + (int)h;
-        lds[(n1 * F::N2 + k2) * TX + t] = v[m] * tw_at<SIGN>(tw, n1 * k2);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < F::N2; ++j) v[j] = lds[(p * F::N2 + j) * TX + t];
-    __syncthreads();
-    reg_dft<SIGN, F::N2, T>(v);
-}
-template <int L>
-__device__ __forceinline__ int pair_spectral_index(int p, int i) {
-    using F = FourStepPair<L>;
-    return (p >> 1) + F::N2 * (i + F::N2 * (p & 1));
-}
-// The split the z pass uses for precision T, length L and table layout: paired at 512 with the octant
-// table (with the half-space table the extra index work would spill, so that case keeps the square
-// split), and at 128 in FP64 (measured at 64^3: FP64 0.249 -> 0.208 ms per 6-RHS launch, FP32 slower).
-template <typename T, int L, bool HALF>
-constexpr bool z_paired() {
-    return (L == 512 || (L == 128 && sizeof(T) == 8)) && !HALF;
-}
-template <typename T, int L, bool HALF>
-struct ZSplit : std::conditional_t<z_paired<T, L, HALF>(), FourStepPair<L>, FourStep<L>> {};
-template <typename T, int L, int TX, int SIGN, bool PAIRED, bool HALF_IN = false>
-__device__ __forceinline__ void z_forward(cpx<T>* v, cpx<T>* lds, const cpx<T>* __restrict__ tw, int t, int q) {
-    if constexpr (PAIRED)
-        fsp_forward<T, L, TX, SIGN, HALF_IN>(v, lds, tw, t, q);
-    else
-        fs_forward<T, L, TX, SIGN, HALF_IN>(v, lds, tw, t, q);
-}
-template <typename T, int L, int TX, int SIGN, bool PAIRED>
-__device__ __forceinline__ void z_backward(cpx<T>* v, cpx<T>* lds, const cpx<T>* __restrict__ tw, int t, int q) {
-    if constexpr (PAIRED)
-        fsp_backward<T, L, TX, SIGN>(v, lds, tw, t, q);
-    else
-        fs_backward<T, L, TX, SIGN>(v, lds, tw, t, q);
-}
-template <int L, bool PAIRED>
-__device__ __forceinline__ int z_spectral_index(int q, int i) {
-    if constexpr (PAIRED)
-        return pair_spectral_index<L>(q, i);
-    else
-        return spectral_index<L>(q, i);
-}
-
 // XCD-aware block order: hardware hands out workgroups round-robin over the 8 XCDs, so logical
 // block b' = (b mod 8) * ceil(nb / 8) + b / 8 gives every XCD one contiguous range of logical
 // blocks (neighbours in logical order then share that XCD's L2).  Returns -1 for padding blocks.
-__device__ __forceinline__ long long xcd_logical_block(long long b, long long nb_real) {
-    const long long per = (nb_real + 7) / 8;
-    const long long lb = (b % 8) * per + b / 8;
-    return lb < nb_real ? lb : -1;
+__device__ __forceinline__ int xcd_logical_block(unsigned b, unsigned nb_real) {
+    const unsigned per = (nb_real + 7) / 8;
+    const unsigned lb = (b % 8) * per + b / 8;
+    return lb < nb_real ? (int)lb : -1;
 }
 
 }  // namespace ls

@@ -142,7 +142,7 @@ __global__ void k_sample_table(z128* __restrict__ buf, int comp, int L1, int L2,
 }
 
 // copy the octant k_a <= L_a/2 of one transformed component, scaled by 1/(L1 L2 L3), into the
-// component-interleaved table [L3/2+1][L2/2+1][L1/2+1][6]
+// table [L3/2+1][L2/2+1][6][green_pitch]
 __global__ void k_extract_octant(const z128* __restrict__ buf, z128* __restrict__ g, z64* __restrict__ g32, int comp,
                                  int L1, int L2, int L3, double scale) {
     const int O1 = L1 / 2 + 1, O2 = L2 / 2 + 1, O3 = L3 / 2 + 1;
@@ -152,8 +152,9 @@ __global__ void k_extract_octant(const z128* __restrict__ buf, z128* __restrict_
     const int x = (int)(q % O1), y = (int)((q / O1) % O2), z = (int)(q / ((long long)O1 * O2));
     const z128 v = buf[((long long)z * L2 + y) * L1 + x];
     const z128 s = {v.x * scale, v.y * scale};
-    g[q * 6 + comp] = s;
-    if (g32) g32[q * 6 + comp] = {(float)s.x, (float)s.y};
+    const long long row = (long long)z * O2 + y;
+    g[green_index<double>(row, comp, x, green_pitch(L1))] = s;
+    if (g32) g32[green_index<float>(row, comp, x, green_pitch(L1))] = {(float)s.x, (float)s.y};
 }
 
 // b_i(x) = phase * sum_q [ G_ij(x - q) F_j(q)  (x != q);  self/h^3 F_i(q)  (x == q) ]
@@ -457,7 +458,7 @@ __global__ void k_fill_aniso(z128* __restrict__ buf, const z128* __restrict__ gr
     buf[q] = v;
 }
 
-// the half-space k_x <= L1/2 of one transformed component, scaled, into [L3][L2][L1/2+1][6]
+// the half-space k_x <= L1/2 of one transformed component, scaled, into [L3][L2][6][green_pitch]
 __global__ void k_extract_half(const z128* __restrict__ buf, z128* __restrict__ g, z64* __restrict__ g32, int comp,
                                int L1, int L2, int L3, double scale) {
     const int O1 = L1 / 2 + 1;
@@ -467,8 +468,9 @@ __global__ void k_extract_half(const z128* __restrict__ buf, z128* __restrict__ 
     const int x = (int)(q % O1), y = (int)((q / O1) % L2), z = (int)(q / ((long long)O1 * L2));
     const z128 v = buf[((long long)z * L2 + y) * L1 + x];
     const z128 s = {v.x * scale, v.y * scale};
-    g[q * 6 + comp] = s;
-    if (g32) g32[q * 6 + comp] = {(float)s.x, (float)s.y};
+    const long long row = (long long)z * L2 + y;
+    g[green_index<double>(row, comp, x, green_pitch(L1))] = s;
+    if (g32) g32[green_index<float>(row, comp, x, green_pitch(L1))] = {(float)s.x, (float)s.y};
 }
 
 // Gauss-Legendre nodes and weights of n points on [-1, 1] (Newton's method on P_n from the
