@@ -207,6 +207,13 @@ using namespace ls;
 
 namespace {
 
+// the smallest 2^a or 3 2^a from 16 to 512 that is at least 2 n - 1
+int smooth_length(int n) {
+    int L = 16;
+    while (L < 2 * n - 1) L = L % 3 == 0 ? L / 3 * 4 : L == 16 ? 32 : L / 2 * 3;
+    return L;
+}
+
 int check_ctx(const ls_ctx* c) {
     if (!c) return fail(LS_ERR_ARG, "null context");
     return LS_OK;
@@ -695,7 +702,8 @@ int ls_apply_noalloc(ls_ctx* c, int i_omega, const void* u, void* Au, int n_rhs)
     if (!u || !Au) return fail(LS_ERR_ARG, "null field pointer");
     if (n_rhs < 1 || n_rhs > c->max_rhs) return fail(LS_ERR_ARG, "n_rhs outside [1, max_rhs]");
     if ((rc = check_disjoint(c, u, Au, n_rhs, sizeof(z128), "ls_apply_noalloc"))) return rc;
-    const size_t work = (size_t)n_rhs * 3 * c->n3 * c->L2 * c->L1 * sizeof(z128);
+    // the limit is stated for lengths 2^a and 3 2^a, which the lengths in use (supported_fft_length) never exceed
+    const size_t work = (size_t)n_rhs * 3 * c->n3 * smooth_length(c->n2) * smooth_length(c->n1) * sizeof(z128);
     const size_t tau = use_fused_contrast() ? 0 : (size_t)n_rhs * 6 * (size_t)c->ncell * sizeof(z128);
     const size_t work_al = (work + 255) / 256 * 256;
     if (work_al + tau > kScratchBytes)

@@ -179,8 +179,8 @@ __global__ __launch_bounds__(TX * FourStep<L>::N1) void k_fs_strided(cpx<T>* __r
     }
 }
 
-// Strided pass at the lengths with a factor 3: the asymmetric four-step of k_fs_zgreen3 (L = A x 16, A = 3, 6,
-// 12, 16 threads per column) for one component, without the Green multiply.  Forward: natural input (threads
+// Strided pass at the lengths L = A x 16, A no power of two (3, 5, 6, 7, 9, 10, 12, 14): the asymmetric four-step of the
+// z pass (fft_z.hip) over 16 threads per column.  Forward: natural input (threads
 // q < A hold elements q + A j), outputs X[q + 16 k1] in slot k1; inverse: the reverse, natural outputs.
 // Threads q >= A transform zeros or a copy of row A - 1 and write nothing (no divergent merge).
 template <typename T, int L, int TX, int SIGN, bool PRUNE>
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(TX * 16) void k_fs_strided3(cpx<T>* __restrict__ da
                                                           long long ES, int n_in, int n_out,
                                                           const cpx<T>* __restrict__ tw) {
     constexpr int B = 16, A = L / B;
-    static_assert(A * B == L && (A == 3 || A == 6 || A == 12), "lengths 48, 96, 192");
+    static_assert(A * B == L && A <= B, "lengths up to 256");
     __shared__ cpx<T> lds[L * TX];
     __shared__ cpx<T> tws[L];
     const int tid = threadIdx.x, t = tid % TX, q = tid / TX;
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(TX * 16) void k_fs_strided3(cpx<T>* __restrict__ da
         __syncthreads();
 #pragma unroll
         for (int n1 = 0; n1 < A; ++n1) v[n1] = lds[(q * A + n1) * TX + t];
-        reg_dft3<SIGN, A, T>(v);
+        reg_dft_any<SIGN, A, T>(v);
 #pragma unroll
         for (int k1 = 0; k1 < A; ++k1) {
             const int k = q + B * k1;
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(TX * 16) void k_fs_strided3(cpx<T>* __restrict__ da
             v[k1] = k < n_in ? load_nt(&base[k * ES]) : cpx<T>{T(0), T(0)};
         }
         __syncthreads();
-        reg_dft3<SIGN, A, T>(v);
+        reg_dft_any<SIGN, A, T>(v);
 #pragma unroll
         for (int n1 = 1; n1 < A; ++n1) v[n1] = v[n1] * tw_at<SIGN>(tws, n1 * q);
 #pragma unroll
@@ -246,13 +246,14 @@ __global__ __launch_bounds__(TX * 16) void k_fs_strided3(cpx<T>* __restrict__ da
     }
 }
 
-// Strided pass at length 384 = 24 x 16: the paired asymmetric four-step of k_fs_zgreen3p for one component.
-// Forward: thread p = 2 k2 + h ends with X[k2 + 16 (i + 12 h)] in slot i; inverse: the reverse.
-template <typename T, int TX, int SIGN, bool PRUNE>
+// Strided pass at L = A x 16, A = 18, 20, 24, 28: the paired asymmetric four-step of the z pass (fft_z.hip), H = A/2.
+// Forward: thread p = 2 k2 + h ends with X[k2 + 16 (i + H h)] in slot i; inverse: the reverse.
+template <typename T, int L, int TX, int SIGN, bool PRUNE>
 __global__ __launch_bounds__(TX * 32) void k_fs_strided3p(cpx<T>* __restrict__ data, long long S1, long long S2,
                                                            long long ES, int n_in, int n_out,
                                                            const cpx<T>* __restrict__ tw) {
-    constexpr int L = 384, B = 16, A = 24, H = 12;
+    constexpr int B = 16, A = L / B, H = A / 2;
+    static_assert(A * B == L && A % 2 == 0 && A <= 32, "lengths above 256");
     static_assert(2 * TX <= 64, "partner lanes share a wavefront");
     __shared__ cpx<T> lds[L * TX];
     __shared__ cpx<T> tws[L];
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(TX * 32) void k_fs_strided3p(cpx<T>* __restrict__ d
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < H; ++m) v[m] = lds[(k2 * A + 2 * m + (int)h) * TX + t];
-        reg_dft3<SIGN, H, T>(v);
+        reg_dft_any<SIGN, H, T>(v);
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             cpx<T> mine = v[i];
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(TX * 32) void k_fs_strided3p(cpx<T>* __restrict__ d
             const cpx<T> dw = (i > 0) ? d * tw_at<SIGN>(tws, i * B) : d;
             v[i] = sel(h, dw, mine + other);
         }
-        reg_dft3<SIGN, H, T>(v);
+        reg_dft_any<SIGN, H, T>(v);
 #pragma unroll
         for (int m = 0; m < H; ++m) {
             const int n1 = 2 * m + (int)h;
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(TY * FourStep<L>::N1) void k_fs_contig(cpx<T>* __re
     }
 }
 
-// Contiguous (x) pass at the lengths with a factor 3 (L = A x 16, A = 3, 6, 12): the asymmetric four-step of
+// Contiguous (x) pass at L = A x 16, A no power of two, up to 256: the asymmetric four-step of
 // k_fs_strided3 along lines, 16 threads per line (thread q = tid mod 16) and TY lines per block; MODE and DOT
 // as in k_fs_contig.  Threads q >= A transform zeros or a copy of element row A - 1 and write nothing.
 template <typename T, int L, int TY, int SIGN, int MODE, bool PRUNE, int DOT = 0>
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(TY * 16) void k_fs_contig3(cpx<T>* __restrict__ dat
                                                          double* __restrict__ dot_parts, long long dot_lines,
                                                          int dot_nparts, int zbs, SlotMap sm, long long lpr) {
     constexpr int B = 16, A = L / B;
-    static_assert(A * B == L && (A == 3 || A == 6 || A == 12), "lengths 48, 96, 192");
+    static_assert(A * B == L && A <= B, "lengths up to 256");
     constexpr int LDP = TY + 1;
     __shared__ cpx<T> lds[L * LDP];
     __shared__ cpx<T> tws[L];
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(TY * 16) void k_fs_contig3(cpx<T>* __restrict__ dat
         __syncthreads();
 #pragma unroll
         for (int n1 = 0; n1 < A; ++n1) v[n1] = lds[(q * A + n1) * LDP + ln];
-        reg_dft3<SIGN, A, T>(v);
+        reg_dft_any<SIGN, A, T>(v);
         if (valid) {
 #pragma unroll
             for (int k1 = 0; k1 < A; ++k1) {
@@ -535,7 +536,7 @@ __global__ __launch_bounds__(TY * 16) void k_fs_contig3(cpx<T>* __restrict__ dat
             ap[j] = (ok && DOT == 1) ? load_nt(&dot_a[orow * n_out + e]) : cpx<T>{T(0), T(0)};
         }
         __syncthreads();
-        reg_dft3<SIGN, A, T>(v);
+        reg_dft_any<SIGN, A, T>(v);
 #pragma unroll
         for (int n1 = 1; n1 < A; ++n1) v[n1] = v[n1] * tw_at<SIGN>(tws, n1 * q);
 #pragma unroll
@@ -557,16 +558,17 @@ __global__ __launch_bounds__(TY * 16) void k_fs_contig3(cpx<T>* __restrict__ dat
     }
 }
 
-// Contiguous (x) pass at length 384 = 24 x 16: the paired asymmetric four-step of k_fs_strided3p along lines,
+// Contiguous (x) pass at L = A x 16, A = 18, 20, 24, 28: the paired asymmetric four-step of k_fs_strided3p along lines,
 // 32 threads per line (thread p = tid mod 32, partner p ^ 1 one lane away); MODE and DOT as in k_fs_contig.
-template <typename T, int TY, int SIGN, int MODE, bool PRUNE, int DOT = 0>
+template <typename T, int L, int TY, int SIGN, int MODE, bool PRUNE, int DOT = 0>
 __global__ __launch_bounds__(TY * 32) void k_fs_contig3p(cpx<T>* __restrict__ data, long long nlines, int D2,
                                                           long long S1, long long S2, int n_in, int n_out,
                                                           const cpx<T>* __restrict__ tw, const cpx<T>* __restrict__ u,
                                                           cpx<T>* __restrict__ out, const cpx<T>* __restrict__ dot_a,
                                                           double* __restrict__ dot_parts, long long dot_lines,
                                                           int dot_nparts, int zbs, SlotMap sm, long long lpr) {
-    constexpr int L = 384, B = 16, A = 24, H = 12, NL = 32;
+    constexpr int B = 16, A = L / B, H = A / 2, NL = 32;
+    static_assert(A * B == L && A % 2 == 0 && A <= 32, "lengths above 256");
     constexpr int LDP = TY + 1;
     __shared__ cpx<T> lds[L * LDP];
     __shared__ cpx<T> tws[L];
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(TY * 32) void k_fs_contig3p(cpx<T>* __restrict__ da
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < H; ++m) v[m] = lds[(k2 * A + 2 * m + (int)h) * LDP + ln];
-        reg_dft3<SIGN, H, T>(v);
+        reg_dft_any<SIGN, H, T>(v);
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             cpx<T> mine = v[i];
@@ -633,7 +635,7 @@ __global__ __launch_bounds__(TY * 32) void k_fs_contig3p(cpx<T>* __restrict__ da
             const cpx<T> dw = (i > 0) ? d * tw_at<SIGN>(tws, i * B) : d;
             v[i] = sel(h, dw, mine + other);
         }
-        reg_dft3<SIGN, H, T>(v);
+        reg_dft_any<SIGN, H, T>(v);
 #pragma unroll
         for (int m = 0; m < H; ++m) {
             const int n1 = 2 * m + (int)h;
@@ -670,12 +672,12 @@ int launch_contig(Ctx* c, int L, cpx<T>* data, long long nlines, int D2, long lo
     switch (L) {
 #define CASE(LL)                                                                                             \
     case LL: {                                                                                               \
-        if constexpr (LL == 48 || LL == 96 || LL == 192 || LL == 384) {                                      \
+        if constexpr (asym_length(LL)) {                                                                     \
             if (fs) {                                                                                        \
                 constexpr int TY = seg_cols<T>();                                                            \
                 const long long nb = (nlines + TY - 1) / TY;                                                 \
-                if constexpr (LL == 384)                                                                     \
-                    hipLaunchKernelGGL((k_fs_contig3p<T, TY, SIGN, MODE, PRUNE, DOT>), dim3((unsigned)nb),   \
+                if constexpr (LL > 256)                                                                      \
+                    hipLaunchKernelGGL((k_fs_contig3p<T, LL, TY, SIGN, MODE, PRUNE, DOT>), dim3((unsigned)nb),   \
                                        dim3(TY * 32), 0, c->stream, data, nlines, D2, S1, S2, n_in, n_out,   \
                                        tw, u, out, (const cpx<T>*)c->dot.a, c->dot.parts, c->dot.lines,      \
                                        c->dot.nparts, zbs, sm, lpr);                                         \
@@ -715,7 +717,7 @@ int launch_contig(Ctx* c, int L, cpx<T>* data, long long nlines, int D2, long lo
     return LS_OK;
 }
 
-// Strided passes at the powers of two from 64 to 256 and at 48, 96 and 192 take tiles of twice the columns (256-byte
+// Strided passes at the powers of two from 64 to 256 and at the other lengths up to 256 take tiles of twice the columns (256-byte
 // segments, twice the threads, the same 16 values per thread) where the x length allows: a plain copy with that
 // access pattern moves 5.62 TB/s against 5.23 with 128-byte segments.  Measured on 6-RHS applies: FP32 y passes
 // per chunk of 2 right-hand sides at 128^3 0.099 -> 0.097 ms (forward) and 0.113 -> 0.108 ms (inverse), y
@@ -725,10 +727,10 @@ template <typename T, int L>
 constexpr bool strided_wide() {
     return L >= 64 && L <= 256 && (L & (L - 1)) == 0;
 }
-// the factor-3 kernel (k_fs_strided3)
+// the asymmetric four-step kernel (k_fs_strided3)
 template <typename T, int L>
 constexpr bool strided3_wide() {
-    return L == 48 || L == 96 || L == 192;
+    return asym_length(L) && L < 256;
 }
 
 template <typename T, int SIGN, bool PRUNE>
@@ -750,16 +752,16 @@ int launch_strided(Ctx* c, int L, cpx<T>* data, int NX, int D2, int D1, long lon
                 break;                                                                                       \
             }                                                                                                \
         }                                                                                                    \
-        if constexpr (LL == 48 || LL == 96 || LL == 192) {                                                   \
+        if constexpr (asym_length(LL) && LL < 256) {                                                         \
             if (fs) {                                                                                        \
                 hipLaunchKernelGGL((k_fs_strided3<T, LL, TX, SIGN, PRUNE>), dim3(NX / TX, D2, D1),           \
                                    dim3(TX * 16), 0, c->stream, data, S1, S2, ES, n_in, n_out, tw);          \
                 break;                                                                                       \
             }                                                                                                \
         }                                                                                                    \
-        if constexpr (LL == 384) {                                                                           \
+        if constexpr (asym_length(LL) && LL > 256) {                                                         \
             if (fs) {                                                                                        \
-                hipLaunchKernelGGL((k_fs_strided3p<T, TX, SIGN, PRUNE>), dim3(NX / TX, D2, D1),              \
+                hipLaunchKernelGGL((k_fs_strided3p<T, LL, TX, SIGN, PRUNE>), dim3(NX / TX, D2, D1),              \
                                    dim3(TX * 32), 0, c->stream, data, S1, S2, ES, n_in, n_out, tw);          \
                 break;                                                                                       \
             }                                                                                                \
@@ -804,11 +806,11 @@ bool use_fourstep() {
     return fs;
 }
 
-// the smallest supported length (2^a or 3 * 2^a, 16..512) that holds the linear convolution of n cells
+// the smallest supported length that holds the linear convolution of n cells
 int supported_fft_length(int n) {
-    static const int lengths[] = {16, 32, 48, 64, 96, 128, 192, 256, 384, 512};
-    for (int L : lengths)
-        if (L >= 2 * n - 1) return L;
+#define TAKE(L) if (L >= 2 * n - 1) return L;
+    LS_FOR_LENGTHS(TAKE)
+#undef TAKE
     return 0;
 }
 
@@ -1008,7 +1010,7 @@ int fused_dot_blocks(const Ctx* c) {
     switch (c->L1) {
 #define CASE(LL)                                                         \
     case LL:                                                             \
-        if constexpr (LL == 48 || LL == 96 || LL == 192 || LL == 384)   \
+        if constexpr (asym_length(LL))                                   \
             ok = true;  /* 16 or 32 threads x 128-byte tiles */           \
         else if constexpr (fs_ok<T, LL>())                                \
             ok = fs_threads<T, LL>() % 64 == 0;                           \

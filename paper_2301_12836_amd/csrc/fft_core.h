@@ -1,6 +1,6 @@
 // Device building blocks of the Stockham FFT used for the zero-padded convolutions of Eq 21.
 //
-// Lines of length L (2^a or 3 * 2^a) are held in LDS as s[e * LDP + t] (element e of line t,
+// Lines of length L (a power of two times 1, 3, 5, 7 or 9) are held in LDS as s[e * LDP + t] (element e of line t,
 // line index fastest).  Each stage reads R elements spaced L/R apart, applies the twiddles
 // W_{Ns R}^{r k} (k = j mod Ns), a radix-R DFT in registers, and writes them back spaced Ns
 // apart from (j / Ns) Ns R + k: the self-sorting (Stockham) form, so no bit reversal is needed.
@@ -101,10 +101,65 @@ struct SmallDft<SIGN, 8, T> {
     }
 };
 
-// the factor 3 first (at NS = 1 it needs no twiddles), then 8, 4, 2
+// DFT of odd length P with sign SIGN, natural order in and out: X_j and X_{P-j} are the sum and the difference of
+// v_0 + sum_k cos(2 pi j k / P) (v_k + v_{P-k}) and SIGN i sum_k sin(2 pi j k / P) (v_k - v_{P-k}), k <= P/2.
+// cos and sin of 2 pi m / P for m = 0..P/2
+template <int P>
+struct OddRoots;
+template <>
+struct OddRoots<5> {
+    static constexpr double c[3] = {1.0, 0.30901699437494742410229341718282, -0.80901699437494742410229341718282};
+    static constexpr double s[3] = {0.0, 0.95105651629515357211643933337938, 0.58778525229247312916870595463907};
+};
+template <>
+struct OddRoots<7> {
+    static constexpr double c[4] = {1.0, 0.62348980185873353052500488400424, -0.22252093395631440428890256449679,
+                                    -0.90096886790241912623610231950745};
+    static constexpr double s[4] = {0.0, 0.78183148246802980870844452667406, 0.97492791218182360701813168299393,
+                                    0.43388373911755812047576833284836};
+};
+template <int SIGN, int P, typename T>
+__device__ __forceinline__ void odd_dft(cpx<T>* v) {
+    constexpr int K = P / 2;
+    using R = OddRoots<P>;
+    cpx<T> t[K + 1], d[K + 1];
+#pragma unroll
+    for (int k = 1; k <= K; ++k) {
+        t[k] = v[k] + v[P - k];
+        d[k] = v[k] - v[P - k];
+    }
+    const cpx<T> v0 = v[0];
+#pragma unroll
+    for (int k = 1; k <= K; ++k) v[0] = v[0] + t[k];
+#pragma unroll
+    for (int j = 1; j <= K; ++j) {
+        cpx<T> m = v0, n = {T(0), T(0)};
+#pragma unroll
+        for (int k = 1; k <= K; ++k) {
+            const int a = (j * k) % P;
+            const T c = T(R::c[a <= K ? a : P - a]), s = T(a <= K ? R::s[a] : -R::s[P - a]);
+            m = m + c * t[k];
+            n = n + s * d[k];
+        }
+        n = mul_si<SIGN>(n);
+        v[j] = m + n;
+        v[P - j] = m - n;
+    }
+}
+
+template <int SIGN, typename T>
+struct SmallDft<SIGN, 5, T> {
+    static __device__ __forceinline__ void run(cpx<T>* v) { odd_dft<SIGN, 5, T>(v); }
+};
+template <int SIGN, typename T>
+struct SmallDft<SIGN, 7, T> {
+    static __device__ __forceinline__ void run(cpx<T>* v) { odd_dft<SIGN, 7, T>(v); }
+};
+
+// the odd factors first (at NS = 1 the first needs no twiddles), then 8, 4, 2
 template <int REM>
 constexpr int pick_radix() {
-    return (REM % 3 == 0) ? 3 : (REM % 8 == 0 && REM != 16) ? 8 : ((REM % 4 == 0) ? 4 : 2);
+    return (REM % 3 == 0) ? 3 : (REM % 5 == 0) ? 5 : (REM % 7 == 0) ? 7 : (REM % 8 == 0 && REM != 16) ? 8 : ((REM % 4 == 0) ? 4 : 2);
 }
 
 // One Stockham stage over NL lines of length L in LDS (leading dimension LDP), NT threads.

@@ -9,8 +9,13 @@ namespace ls {
 
 constexpr int kThreads = 256;   // threads per block of the LDS Stockham kernels
 
-// supported FFT lengths
-#define LS_FOR_LENGTHS(X) X(16) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512)
+// Supported FFT lengths: multiples of 16 whose quotient has register DFTs.  A grid of n cells per axis takes the
+// smallest one >= 2 n - 1; neighbours differ by at most a quarter above 64 (a third at 192 with only 2^a and 3 2^a).
+#define LS_FOR_LENGTHS(X)                                                                              \
+    X(16) X(32) X(48) X(64) X(80) X(96) X(112) X(128) X(144) X(160) X(192) X(224) X(256) X(288) X(320) \
+    X(384) X(448) X(512)
+// lengths L = A x 16 whose A is no power of two: the asymmetric four-step kernels (k_fs_*3 to 256, k_fs_*3p above)
+constexpr bool asym_length(int L) { return (L & (L - 1)) != 0; }
 
 // Adjacent columns (lines, in the x passes) of a register four-step block: 128-byte row segments.
 template <typename T>

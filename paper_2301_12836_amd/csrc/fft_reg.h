@@ -205,49 +205,49 @@ __device__ __forceinline__ void reg_dft3(cpx<T>* v) {
     }
 }
 
-// DFT of odd length P with sign SIGN, natural order in and out: X_j and X_{P-j} are the sum and the difference of
-// v_0 + sum_k cos(2 pi j k / P) (v_k + v_{P-k}) and SIGN i sum_k sin(2 pi j k / P) (v_k - v_{P-k}), k <= P/2.
-// cos and sin of 2 pi m / P for m = 0..P/2
-template <int P>
-struct OddRoots;
+// cos and sin of 2 pi m / N
+template <int N>
+struct Roots;
 template <>
-struct OddRoots<5> {
-    static constexpr double c[3] = {1.0, 0.30901699437494742410229341718282, -0.80901699437494742410229341718282};
-    static constexpr double s[3] = {0.0, 0.95105651629515357211643933337938, 0.58778525229247312916870595463907};
+struct Roots<9> {
+    static constexpr double c[5] = {1.0, 0.766044443118978, 0.17364817766693041, -0.4999999999999998, -0.9396926207859083};
+    static constexpr double s[5] = {0.0, 0.6427876096865393, 0.984807753012208, 0.8660254037844387, 0.3420201433256689};
 };
 template <>
-struct OddRoots<7> {
-    static constexpr double c[4] = {1.0, 0.62348980185873353052500488400424, -0.22252093395631440428890256449679,
-                                    -0.90096886790241912623610231950745};
-    static constexpr double s[4] = {0.0, 0.78183148246802980870844452667406, 0.97492791218182360701813168299393,
-                                    0.43388373911755812047576833284836};
+struct Roots<10> {
+    static constexpr double c[5] = {1.0, 0.8090169943749475, 0.30901699437494745, -0.30901699437494734, -0.8090169943749473};
+    static constexpr double s[5] = {0.0, 0.5877852522924731, 0.9510565162951535, 0.9510565162951536, 0.5877852522924732};
 };
-template <int SIGN, int P, typename T>
-__device__ __forceinline__ void odd_dft(cpx<T>* v) {
-    constexpr int K = P / 2;
-    using R = OddRoots<P>;
-    cpx<T> t[K + 1], d[K + 1];
+template <>
+struct Roots<14> {
+    static constexpr double c[7] = {1.0, 0.9009688679024191, 0.6234898018587336, 0.22252093395631445, -0.22252093395631434, -0.6234898018587335, -0.900968867902419};
+    static constexpr double s[7] = {0.0, 0.4338837391175581, 0.7818314824680298, 0.9749279121818236, 0.9749279121818236, 0.7818314824680299, 0.43388373911755823};
+};
+
+// In-register DFT of length N = P Q (9, 10, 14) with sign SIGN, natural order in and out: with n = a + P b and
+// k = k2 + Q k1, length-Q DFTs of each residue a, the twiddles W_N^{a k2}, then length-P DFTs.
+template <int SIGN, int P, int Q, typename T>
+__device__ __forceinline__ void reg_dft_pq(cpx<T>* v) {
+    constexpr int N = P * Q;
+    cpx<T> tmp[N];
 #pragma unroll
-    for (int k = 1; k <= K; ++k) {
-        t[k] = v[k] + v[P - k];
-        d[k] = v[k] - v[P - k];
+    for (int a = 0; a < P; ++a) {
+        cpx<T> w[Q];
+#pragma unroll
+        for (int b = 0; b < Q; ++b) w[b] = v[a + P * b];
+        SmallDft<SIGN, Q, T>::run(w);
+#pragma unroll
+        for (int k2 = 0; k2 < Q; ++k2)
+            tmp[a * Q + k2] = (a * k2 == 0) ? w[k2] : w[k2] * cpx<T>{T(Roots<N>::c[a * k2]), T(SIGN * Roots<N>::s[a * k2])};
     }
-    const cpx<T> v0 = v[0];
 #pragma unroll
-    for (int k = 1; k <= K; ++k) v[0] = v[0] + t[k];
+    for (int k2 = 0; k2 < Q; ++k2) {
+        cpx<T> w[P];
 #pragma unroll
-    for (int j = 1; j <= K; ++j) {
-        cpx<T> m = v0, n = {T(0), T(0)};
+        for (int a = 0; a < P; ++a) w[a] = tmp[a * Q + k2];
+        SmallDft<SIGN, P, T>::run(w);
 #pragma unroll
-        for (int k = 1; k <= K; ++k) {
-            const int a = (j * k) % P;
-            const T c = T(R::c[a <= K ? a : P - a]), s = T(a <= K ? R::s[a] : -R::s[P - a]);
-            m = m + c * t[k];
-            n = n + s * d[k];
-        }
-        n = mul_si<SIGN>(n);
-        v[j] = m + n;
-        v[P - j] = m - n;
+        for (int k1 = 0; k1 < P; ++k1) v[k2 + Q * k1] = w[k1];
     }
 }
 
@@ -259,8 +259,12 @@ __device__ __forceinline__ void reg_dft_any(cpx<T>* v) {
         reg_dft<SIGN, N, T>(v);
     else if constexpr (N == 3 || N == 6 || N == 12)
         reg_dft3<SIGN, N, T>(v);
+    else if constexpr (N == 9)
+        reg_dft_pq<SIGN, 3, 3, T>(v);
+    else if constexpr (N == 10 || N == 14)
+        reg_dft_pq<SIGN, 2, N / 2, T>(v);
     else
-        odd_dft<SIGN, N, T>(v);
+        SmallDft<SIGN, N, T>::run(v);
 }
 
 template <int L>

@@ -174,12 +174,13 @@ struct ZLine {
 };
 
 // Waves per SIMD of the register z pass.  FP64 at 384 needs 75 registers more than two waves leave: 3.02 ms (2
-// right-hand sides at 192^3) against 2.54 ms with one wave; the half-space table's index work at 512 as many.  FP32
+// right-hand sides at 192^3) against 2.54 ms with one wave; 224 (3 at 112^3: 0.61 against 0.54 ms) and 448 60 and 170;
+// the half-space table's index work at 512 as many.  At 320 the two waves pay (160^3 0.72 against 0.81 ms).  FP32
 // with four waves spills as well (0.86 against 0.74 ms at 128^3).
 template <typename T, int L, bool HALF>
 constexpr int z_waves() {
     constexpr bool big = L == 512 && HALF;
-    return sizeof(T) == 8 ? (L == 384 || big ? 1 : 2) : (big ? 2 : 3);
+    return sizeof(T) == 8 ? (L == 224 || L == 384 || L == 448 || big ? 1 : 2) : (big ? 2 : 3);
 }
 
 // Scheduling fence between the components of the register z pass: above 256 it saves the registers of the second wave
