@@ -366,6 +366,12 @@ int ls_kernel_schedule(const ls_ctx* ctx, int* schedule);
  * or LS_ERR_ARG for a null context. */
 int ls_contrast_format(const ls_ctx* ctx);
 
+/* The hipStream_t the context's work runs on: the one it was set up with or, set up on the null stream, a private
+ * blocking stream (ordered with the null stream, not with other contexts' private streams).  A stream-ordered
+ * allocator that takes the outputs of asynchronous calls from this stream's pool hands the memory of a dropped
+ * output only to later work of the same context.  NULL for a null context. */
+void* ls_stream(const ls_ctx* ctx);
+
 /* Message of the last error on this host thread ("" if none). */
 const char* ls_last_error(void);
 

@@ -1067,6 +1067,8 @@ int ls_profile_read(ls_ctx* c, char* names, int* counts, double* ms, long long* 
 
 long long ls_device_bytes(const ls_ctx* c) { return c ? c->bytes : 0; }
 
+void* ls_stream(const ls_ctx* c) { return c ? (void*)c->stream : nullptr; }
+
 int ls_contrast_format(const ls_ctx* c) {
     if (!c) return fail(LS_ERR_ARG, "null context");
     return c->contrast_k;

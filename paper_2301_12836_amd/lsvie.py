@@ -13,6 +13,7 @@ them for convenience, and ``solve_batch`` wraps ``ls_solve_batch`` over several 
 """
 
 import ctypes
+import math
 import os
 
 import numpy as np
@@ -47,7 +48,7 @@ ERROR_NAMES = {LS_ERR_ARG: "LS_ERR_ARG", LS_ERR_OOM: "LS_ERR_OOM", LS_ERR_HIP: "
 EXPORTED = ("ls_setup", "ls_destroy", "ls_apply", "ls_apply_noalloc", "ls_apply_c64", "ls_rhs_moment", "ls_rhs_force", "ls_solve",
             "ls_solve_moment", "ls_solve_multi", "ls_solve_force", "ls_strain", "ls_set_contrast", "ls_precond_blocks", "ls_apply_T", "ls_convolve",
             "ls_solve_T", "ls_grad_contrast", "ls_grad", "ls_solve_batch", "ls_sample", "ls_synthesize", "ls_residual_history",
-            "ls_profile", "ls_profile_read", "ls_device_bytes", "ls_kernel_variants", "ls_kernel_schedule", "ls_contrast_format", "ls_last_error")
+            "ls_profile", "ls_profile_read", "ls_device_bytes", "ls_kernel_variants", "ls_kernel_schedule", "ls_contrast_format", "ls_stream", "ls_last_error")
 
 
 class LsError(RuntimeError):
@@ -129,6 +130,7 @@ def load():
         "ls_kernel_variants": (I, [P, ip]),
         "ls_kernel_schedule": (I, [P, ip]),
         "ls_contrast_format": (I, [P]),
+        "ls_stream": (P, [P]),
         "ls_last_error": (ctypes.c_char_p, []),
     }
     for name, (res, args) in sig.items():
@@ -391,6 +393,11 @@ def ls_contrast_format(ctx):
     return k
 
 
+def ls_stream(ctx):
+    """The context's stream as an integer handle."""
+    return load().ls_stream(ctx) or 0
+
+
 def ls_kernel_variants(ctx):
     v = (ctypes.c_int * 10)()
     _check(load().ls_kernel_variants(ctx, v))
@@ -440,6 +447,12 @@ class Context:
                                (0 if graphs else LS_FLAG_NO_GRAPH) | (LS_FLAG_AUTOTUNE if autotune else 0),
                                int(taper), int(bicgstab_l), PRECONDS[precond])
         del dc, dr
+        # On the default stream the library works on a private one.  Outputs are allocated on that stream, so that the
+        # allocator hands a dropped output's memory only to later work of this context: work of another context
+        # is not ordered with what may still be writing it.
+        own = ls_stream(self.handle)
+        self._pool = torch.cuda.ExternalStream(own, device=self.device) if self.stream.cuda_stream == 0 else None
+        self._index = self._device_index().index
 
     def close(self):
         if self.handle is not None:
@@ -470,16 +483,19 @@ class Context:
     # helpers
     def _field(self, t, dtype=None):
         torch = self.torch
-        t = torch.as_tensor(t, device=self.device)
+        if not isinstance(t, torch.Tensor) or t.device.index != self._index:
+            t = torch.as_tensor(t, device=self.device)
         if dtype is not None:
-            t = t.to(dtype)
-        if t.dtype not in (torch.complex128, torch.complex64):
+            if t.dtype != dtype:
+                t = t.to(dtype)
+        elif t.dtype not in (torch.complex128, torch.complex64):
             t = t.to(torch.complex128)
         # lazy conjugate / negative views keep the original data behind data_ptr(): materialise them
-        t = t.resolve_conj().resolve_neg().contiguous()
+        if t.is_conj() or t.is_neg() or not t.is_contiguous():
+            t = t.resolve_conj().resolve_neg().contiguous()
         if t.shape[-4:] != self.field_shape:
             raise ValueError(f"field shape {tuple(t.shape)} does not end in {self.field_shape}")
-        nrhs = 1 if t.dim() == 4 else int(np.prod(t.shape[:-4]))
+        nrhs = 1 if t.dim() == 4 else math.prod(t.shape[:-4])
         return t, nrhs
 
     def _check(self, t, shape, dtype, name="out"):
@@ -493,11 +509,25 @@ class Context:
         """A fresh output like the (already converted) input, or the caller's buffer once checked (it must
         not share memory with the input: the library reads the input while it writes the output)."""
         if out is None:
-            return self.torch.empty_like(like)
+            return self._new(self.torch.empty_like, like)
         self._check(out, like.shape, like.dtype)
         if storage_overlaps(out, like):
             raise ValueError("out shares memory with the input")
         return out
+
+    def _new(self, make, *args, **kwargs):
+        """make(*args, **kwargs), an output tensor, from the context's own pool when the caller is on the default stream."""
+        torch = self.torch
+        if self._pool is None or torch._C._cuda_getCurrentRawStream(self._index) != 0:
+            return make(*args, **kwargs)
+        if torch._C._cuda_getDevice() != self._index:   # set_stream would switch the current device
+            with torch.cuda.stream(self._pool):
+                return make(*args, **kwargs)
+        torch.cuda.set_stream(self._pool)
+        try:
+            return make(*args, **kwargs)
+        finally:
+            torch.cuda.set_stream(self.stream)
 
     def empty(self, nrhs=None, dtype=None):
         torch = self.torch
@@ -577,11 +607,11 @@ class Context:
         if nrhs != nrhs2:
             raise ValueError("u and mu must hold the same number of fields")
         if g_dC is None:
-            g_dC = torch.zeros((21,) + self.field_shape[1:], dtype=torch.float64, device=self.device)
+            g_dC = self._new(torch.zeros, (21,) + self.field_shape[1:], dtype=torch.float64, device=self.device)
         else:
             self._check(g_dC, (21,) + self.field_shape[1:], torch.float64, "g_dC")
         if g_drho is None:
-            g_drho = torch.zeros(self.field_shape[1:], dtype=torch.float64, device=self.device)
+            g_drho = self._new(torch.zeros, self.field_shape[1:], dtype=torch.float64, device=self.device)
         else:
             self._check(g_drho, self.field_shape[1:], torch.float64, "g_drho")
         ls_grad_contrast(self.handle, i_omega, u, mu, nrhs, g_dC, g_drho)
@@ -604,11 +634,11 @@ class Context:
         if nrhs != nrhs2:
             raise ValueError("u and lam_bar must hold the same number of fields")
         if g_dC is None:
-            g_dC = torch.zeros((21,) + self.field_shape[1:], dtype=torch.float64, device=self.device)
+            g_dC = self._new(torch.zeros, (21,) + self.field_shape[1:], dtype=torch.float64, device=self.device)
         else:
             self._check(g_dC, (21,) + self.field_shape[1:], torch.float64, "g_dC")
         if g_drho is None:
-            g_drho = torch.zeros(self.field_shape[1:], dtype=torch.float64, device=self.device)
+            g_drho = self._new(torch.zeros, self.field_shape[1:], dtype=torch.float64, device=self.device)
         else:
             self._check(g_drho, self.field_shape[1:], torch.float64, "g_drho")
         gM = ls_grad(self.handle, i_omega, u, lam_bar, nrhs, g_dC, g_drho, src=src, t0=t0)
@@ -635,7 +665,7 @@ class Context:
 
     def strain(self, u):
         u, nrhs = self._field(u, self.torch.complex128)
-        eps = self.torch.empty(u.shape[:-4] + (6,) + self.field_shape[1:], dtype=u.dtype, device=self.device)
+        eps = self._new(self.torch.empty, u.shape[:-4] + (6,) + self.field_shape[1:], dtype=u.dtype, device=self.device)
         ls_strain(self.handle, u, eps, nrhs)
         return eps
 
