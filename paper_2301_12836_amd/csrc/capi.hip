@@ -148,18 +148,14 @@ template <typename T>
 int apply_T_op(Ctx* c, const RhsSet& set, const cpx<T>* y, cpx<T>* ATy) {
     cpx<T>* work = (cpx<T>*)c->work;
     cpx<T>* g = (cpx<T>*)c->gs;
-    int rc = to_work<T>(c, set, y, work);
-    if (rc) return rc;
-    rc = fft_apply_passes<T>(c, set, work, nullptr, g, false);
+    const int rc = fft_apply_passes<T>(c, set, work, nullptr, g, false, y);
     if (rc) return rc;
     return contrast_transposed_epilogue<T>(c, set, g, y, ATy, (cpx<T>*)c->tau);
 }
 
 template <typename T>
 int convolve_op(Ctx* c, const RhsSet& set, const cpx<T>* f, cpx<T>* out) {
-    int rc = to_work<T>(c, set, f, (cpx<T>*)c->work);
-    if (rc) return rc;
-    return fft_apply_passes<T>(c, set, (cpx<T>*)c->work, nullptr, out, false);
+    return fft_apply_passes<T>(c, set, (cpx<T>*)c->work, nullptr, out, false, f);
 }
 
 template int apply_T_op<double>(Ctx*, const RhsSet&, const z128*, z128*);
@@ -764,7 +760,7 @@ int ls_grad_contrast(ls_ctx* c, int i_omega, const void* u, const void* mu, int 
     if ((rc = check_ctx(c)) || (rc = check_omega(c, i_omega))) return rc;
     if (!u || !mu || !g_dC || !g_drho) return fail(LS_ERR_ARG, "null pointer");
     if (n_rhs < 1) return fail(LS_ERR_ARG, "n_rhs must be >= 1");
-    return grad_contrast_launch(c, i_omega, (const z128*)u, (const z128*)mu, n_rhs, g_dC, g_drho);
+    return grad_contrast_launch(c, i_omega, (const z128*)u, (const z128*)mu, false, n_rhs, g_dC, g_drho);
 }
 
 int ls_grad(ls_ctx* c, int i_omega, const void* u, const void* lam_bar, int n_rhs, const int* src, const double* t0,
@@ -780,11 +776,10 @@ int ls_grad(ls_ctx* c, int i_omega, const void* u, const void* lam_bar, int n_rh
             if (!std::isfinite(t0[r])) return fail(LS_ERR_ARG, "non-finite source time");
         }
     }
-    z128* mu = (z128*)c->gs;  // mu = conj(Gconv lam_bar), in the workspace of the transposed operator
-    if ((rc = convolve_op<double>(c, RhsSet::uniform(n_rhs, i_omega), (const z128*)lam_bar, mu))) return rc;
-    if ((rc = conj_launch(c, mu, 3 * c->ncell * n_rhs))) return rc;
-    if ((rc = grad_contrast_launch(c, i_omega, (const z128*)u, mu, n_rhs, g_dC, g_drho))) return rc;
-    if (g_M) return grad_moment_launch(c, i_omega, mu, n_rhs, src, t0, g_M);
+    z128* muc = (z128*)c->gs;  // conj(mu) = Gconv lam_bar, in the workspace of the transposed operator
+    if ((rc = convolve_op<double>(c, RhsSet::uniform(n_rhs, i_omega), (const z128*)lam_bar, muc))) return rc;
+    if ((rc = grad_contrast_launch(c, i_omega, (const z128*)u, muc, true, n_rhs, g_dC, g_drho))) return rc;
+    if (g_M) return grad_moment_launch(c, i_omega, muc, n_rhs, src, t0, g_M);
     return LS_OK;
 }
 

@@ -282,7 +282,8 @@ int dalloc(Ctx* c, void** p, size_t bytes);
 
 // FFT passes over the padded buffer (positions of the set) ending in the compact fields Au (slots); see fft.hip
 template <typename T>
-int fft_apply_passes(Ctx* c, const RhsSet& set, cpx<T>* work, const cpx<T>* u, cpx<T>* Au, bool subtract_from_u);
+int fft_apply_passes(Ctx* c, const RhsSet& set, cpx<T>* work, const cpx<T>* u, cpx<T>* Au, bool subtract_from_u,
+                     const cpx<T>* f = nullptr);   // f: the compact field to convolve, instead of work's contents
 template <typename T>
 int fft_full_3d_forward(Ctx* c, cpx<T>* buf);
 template <typename T>
@@ -300,17 +301,16 @@ int contrast_to_work(Ctx* c, const RhsSet& set, const cpx<T>* u, cpx<T>* work, c
 template <typename T>
 int contrast_transposed_epilogue(Ctx* c, const RhsSet& set, const cpx<T>* g, const cpx<T>* y, cpx<T>* out,
                                  cpx<T>* tau);
-template <typename T>
-int to_work(Ctx* c, const RhsSet& set, const cpx<T>* f, cpx<T>* work);
-int grad_contrast_launch(Ctx* c, int i_omega, const z128* u, const z128* mu, int nrhs, double* g21, double* grho);
+// conjugated: mu holds the conjugate field
+int grad_contrast_launch(Ctx* c, int i_omega, const z128* u, const z128* mu, bool conjugated, int nrhs, double* g21,
+                         double* grho);
 int fold_background(Ctx* c, const double* dc_in, const double* drho_in, const double fold21[21]);
 size_t contrast_packed_elems(const Ctx* c, bool fp32);   // elements of dcp (fp32 false) or dcp32
 bool use_fused_contrast();  // false under LS_CONTRAST=split (the two-kernel contrast, which needs tau)
-int conj_launch(Ctx* c, z128* a, long long m);
 int sample_launch(Ctx* c, const z128* u, int nrhs, const int* rec_host, int nrec, z128* out);
 int synthesize_launch(Ctx* c, const z128* U, const int* k_host, int nf, int ntr, int nt, double dt, double fp,
                       double ts, double* traces);
-int grad_moment_launch(Ctx* c, int i_omega, const z128* mu, int nrhs, const int* src, const double* t0,
+int grad_moment_launch(Ctx* c, int i_omega, const z128* muc, int nrhs, const int* src, const double* t0,
                        double* gM);
 int strain_launch(Ctx* c, const z128* u, z128* eps, int nrhs);
 

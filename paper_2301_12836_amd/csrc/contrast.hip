@@ -28,13 +28,14 @@ __host__ __device__ constexpr int packed(int I, int J) {
 constexpr int kOrtho9[9] = {0, 1, 2, 6, 7, 11, 15, 18, 20};
 constexpr int kOffOrtho[12] = {3, 4, 5, 8, 9, 10, 12, 13, 14, 16, 17, 19};
 
-// d/dx_a at index i of an axis with n cells (Eq 18): central inside, one-sided at the ends
+// d/dx_a at index i of an axis with n cells (Eq 18): central inside, one-sided at the ends.  Both are the difference of
+// the neighbours clamped to the axis, so a wavefront that holds both takes no branch (k_grad_contrast, 3 right-hand
+// sides at 96^3: 278 -> 259 us).
 template <typename T>
 __device__ __forceinline__ cpx<T> deriv(const cpx<T>* __restrict__ f, long long p, long long stride, int i, int n,
                                         T inv_h) {
-    if (i == 0) return inv_h * (f[p + stride] - f[p]);
-    if (i == n - 1) return inv_h * (f[p] - f[p - stride]);
-    return (T(0.5) * inv_h) * (f[p + stride] - f[p - stride]);
+    const bool lo = i == 0, hi = i == n - 1;
+    return (lo || hi ? inv_h : T(0.5) * inv_h) * (f[hi ? p : p + stride] - f[lo ? p : p - stride]);
 }
 
 // (D^T v)(i) along one axis: coefficients of v(i-1), v(i), v(i+1) in row sums of D
@@ -55,25 +56,7 @@ __device__ __forceinline__ cpx<T> deriv_t(const cpx<T>* __restrict__ v, long lon
     return acc;
 }
 
-// Voigt strain at the cell with grid indices (i, j, k) of an N1 x N2 x N3 grid; the field's values sit
-// at element p of three component arrays n apart, with neighbours 1, sy and sz elements away (the
-// grid itself, or a tile of it staged in LDS).
-template <typename T>
-__device__ __forceinline__ void strain_at_strided(const cpx<T>* __restrict__ u, long long n, long long p, int i,
-                                                  int j, int k, long long sy, long long sz, int N1, int N2, int N3,
-                                                  T inv_h, cpx<T> eps[6]) {
-    const long long sx = 1;
-    const cpx<T>* u0 = u;
-    const cpx<T>* u1 = u + n;
-    const cpx<T>* u2 = u + 2 * n;
-    eps[0] = deriv(u0, p, sx, i, N1, inv_h);
-    eps[1] = deriv(u1, p, sy, j, N2, inv_h);
-    eps[2] = deriv(u2, p, sz, k, N3, inv_h);
-    eps[3] = deriv(u1, p, sz, k, N3, inv_h) + deriv(u2, p, sy, j, N2, inv_h);
-    eps[4] = deriv(u0, p, sz, k, N3, inv_h) + deriv(u2, p, sx, i, N1, inv_h);
-    eps[5] = deriv(u0, p, sy, j, N2, inv_h) + deriv(u1, p, sx, i, N1, inv_h);
-}
-
+// Voigt strain at the cell with grid indices (i, j, k) (element p of component arrays n apart)
 template <typename T>
 __device__ __forceinline__ void strain_at(const cpx<T>* __restrict__ u, long long n, long long p, int i, int j,
                                           int k, int N1, int N2, int N3, T inv_h, cpx<T> eps[6]) {
@@ -502,23 +485,6 @@ __global__ void k_off_ortho(const double* __restrict__ dc, long long n, int* __r
         }
 }
 
-// compact field f[slot][c][n] -> zero-padded work buffer at position r (layout of zplane_offset; data cells only)
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_to_work(const cpx<T>* __restrict__ f, cpx<T>* __restrict__ work,
-                                                      SlotMap sm, int nrhs, int N1, int N2, int N3, int L1, int L2,
-                                                      int zbs) {
-    const long long n = (long long)N1 * N2 * N3;
-    const long long p = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (p >= n) return;
-    const int i = (int)(p % N1);
-    const int j = (int)((p / N1) % N2);
-    const int k = (int)(p / ((long long)N1 * N2));
-    const long long cpitch = (long long)N3 * L2 * L1;
-    const long long wpos = zplane_offset(k, zbs, L2, L1) + zrow_offset(j, zbs, L1) + i;
-    for (int r = 0; r < nrhs; ++r)
-        for (int c = 0; c < 3; ++c) work[(3LL * r + c) * cpitch + wpos] = f[(3LL * sm.slot[r] + c) * n + p];
-}
-
 // Absorbing-layer weight of cell (i, j, k) (Eq 23-25): 1 - exp(-l^2 / (N_a h^2)) within d cells of a face,
 // 1 elsewhere; l is the distance from the cell centre to where the ray from the model centre through it
 // leaves the box (faces half a cell outside the outer cell centres), N_a the cell count along the axis of
@@ -544,18 +510,28 @@ __device__ double taper_weight(int i, int j, int k, int N1, int N2, int N3, int 
     return 1.0 - exp(-l * l / n[axis]);
 }
 
+// Re[conj(m) u] from m, or from its conjugate (CONJ)
+template <bool CONJ>
+__device__ __forceinline__ double real_product(z128 m, z128 u) {
+    return CONJ ? m.x * u.x - m.y * u.y : m.x * u.x + m.y * u.y;
+}
+
 // Gradient of a real misfit with respect to the contrast at every cell, for forward fields u and
 // adjoint-side fields mu = conj(Gconv lambda_bar) (lambda_bar solving A^T lambda_bar = conj(P^H r)):
 //   g21[JK](p) += -Re[conj(eps_J(mu)) eps_K(u) + (J != K) conj(eps_K(mu)) eps_J(u)]   (packed J <= K)
 //   grho(p)    += w^2 Re[sum_c conj(mu_c) u_c]
-// summed over the nrhs (u, mu) pairs.
+// summed over the nrhs (u, mu) pairs.  CONJ: the array holds conj(mu).  Bound by its memory traffic (0.57 GB for 3
+// right-hand sides at 96^3, 0.115 ms at 4.9 TB/s); in the XCD-aware block order the neighbours' rows and planes come from
+// the same L2 (259 -> 200 us).
+template <bool CONJ>
 __global__ __launch_bounds__(kThreads) void k_grad_contrast(const z128* __restrict__ u, const z128* __restrict__ mu,
                                                             double* __restrict__ g21, double* __restrict__ grho,
                                                             int nrhs, int N1, int N2, int N3, double inv_h, double w2,
                                                             int taper) {
     const long long n = (long long)N1 * N2 * N3;
-    const long long p = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (p >= n) return;
+    const long long lb = xcd_logical_block(blockIdx.x, (unsigned)((n + kThreads - 1) / kThreads));
+    const long long p = lb * kThreads + threadIdx.x;
+    if (lb < 0 || p >= n) return;
     const int i = (int)(p % N1);
     const int j = (int)((p / N1) % N2);
     const int k = (int)(p / ((long long)N1 * N2));
@@ -573,12 +549,12 @@ __global__ __launch_bounds__(kThreads) void k_grad_contrast(const z128* __restri
         for (int I = 0; I < 6; ++I)
 #pragma unroll
             for (int J = I; J < 6; ++J) {
-                double v = cmulc(em[I], eu[J]).x;
-                if (J != I) v += cmulc(em[J], eu[I]).x;
+                double v = real_product<CONJ>(em[I], eu[J]);
+                if (J != I) v += real_product<CONJ>(em[J], eu[I]);
                 acc[packed(I, J)] -= v;
             }
 #pragma unroll
-        for (int c = 0; c < 3; ++c) ar += cmulc(mr[c * n + p], ur[c * n + p]).x;
+        for (int c = 0; c < 3; ++c) ar += real_product<CONJ>(mr[c * n + p], ur[c * n + p]);
     }
     // the contrast the operator sees is the input times the absorbing-layer weight
     const double tw = taper_weight(i, j, k, N1, N2, N3, taper);
@@ -587,15 +563,9 @@ __global__ __launch_bounds__(kThreads) void k_grad_contrast(const z128* __restri
     grho[p] += tw * w2 * ar;
 }
 
-// a[p] = conj(a[p])
-__global__ void k_conj(z128* __restrict__ a, long long m) {
-    const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < m) a[p].y = -a[p].y;
-}
-
 // Moment-tensor gradient: gM[r][J] = Re[e^{i w t0_r} conj(eps_J(mu_r)(s_r))] / h^3 (one thread per
-// right-hand side; s_r inside the grid, checked on the host)
-__global__ void k_grad_moment(const z128* __restrict__ mu, const int* __restrict__ src, const double* __restrict__ t0,
+// right-hand side; s_r inside the grid, checked on the host), from the conjugate of mu
+__global__ void k_grad_moment(const z128* __restrict__ muc, const int* __restrict__ src, const double* __restrict__ t0,
                               double* __restrict__ gM, int nrhs, int N1, int N2, int N3, double inv_h, double w,
                               double inv_h3) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -604,11 +574,11 @@ __global__ void k_grad_moment(const z128* __restrict__ mu, const int* __restrict
     const int i = src[3 * r], j = src[3 * r + 1], k = src[3 * r + 2];
     const long long p = ((long long)k * N2 + j) * N1 + i;
     z128 eps[6];
-    strain_at(mu + (long long)r * 3 * n, n, p, i, j, k, N1, N2, N3, inv_h, eps);
+    strain_at(muc + (long long)r * 3 * n, n, p, i, j, k, N1, N2, N3, inv_h, eps);
     double sn, cs;
     sincos(w * t0[r], &sn, &cs);
 #pragma unroll
-    for (int J = 0; J < 6; ++J) gM[6 * r + J] = (cs * eps[J].x + sn * eps[J].y) * inv_h3;
+    for (int J = 0; J < 6; ++J) gM[6 * r + J] = (cs * eps[J].x - sn * eps[J].y) * inv_h3;
 }
 
 template <typename T>
@@ -830,42 +800,22 @@ int contrast_transposed_epilogue(Ctx* c, const RhsSet& set, const cpx<T>* g, con
 template int contrast_transposed_epilogue<double>(Ctx*, const RhsSet&, const z128*, const z128*, z128*, z128*);
 template int contrast_transposed_epilogue<float>(Ctx*, const RhsSet&, const z64*, const z64*, z64*, z64*);
 
-template <typename T>
-int to_work(Ctx* c, const RhsSet& set, const cpx<T>* f, cpx<T>* work) {
+int grad_contrast_launch(Ctx* c, int i_omega, const z128* u, const z128* mu, bool conjugated, int nrhs, double* g21,
+                         double* grho) {
     const long long n = c->ncell;
-    const unsigned nb = (unsigned)((n + kThreads - 1) / kThreads);
-    c->prof.begin(c->stream, LS_PNAME(T, "to_work"), set.n);
-    hipLaunchKernelGGL((k_to_work<T>), dim3(nb), dim3(kThreads), 0, c->stream, f, work, slot_map(set), set.n, c->n1,
-                       c->n2, c->n3, c->L1, c->L2, c->zbs);
-    c->prof.end(c->stream);
-    LS_HIP(hipGetLastError());
-    return LS_OK;
-}
-
-template int to_work<double>(Ctx*, const RhsSet&, const z128*, z128*);
-template int to_work<float>(Ctx*, const RhsSet&, const z64*, z64*);
-
-int grad_contrast_launch(Ctx* c, int i_omega, const z128* u, const z128* mu, int nrhs, double* g21, double* grho) {
-    const long long n = c->ncell;
-    const unsigned nb = (unsigned)((n + kThreads - 1) / kThreads);
+    const unsigned nb = (unsigned)(((n + kThreads - 1) / kThreads + 7) / 8 * 8);
     const double w = c->omega[i_omega];
     c->prof.begin(c->stream, "grad_contrast.c128", nrhs);
-    hipLaunchKernelGGL(k_grad_contrast, dim3(nb), dim3(kThreads), 0, c->stream, u, mu, g21, grho, nrhs, c->n1, c->n2,
-                       c->n3, 1.0 / c->h, w * w, c->taper);
+    hipLaunchKernelGGL((conjugated ? k_grad_contrast<true> : k_grad_contrast<false>), dim3(nb), dim3(kThreads), 0, c->stream,
+                       u, mu, g21, grho, nrhs, c->n1, c->n2, c->n3, 1.0 / c->h, w * w, c->taper);
     c->prof.end(c->stream);
-    LS_HIP(hipGetLastError());
-    return LS_OK;
-}
-
-int conj_launch(Ctx* c, z128* a, long long m) {
-    hipLaunchKernelGGL(k_conj, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, c->stream, a, m);
     LS_HIP(hipGetLastError());
     return LS_OK;
 }
 
 // src: host [nrhs][3] cells (inside the grid); t0: host [nrhs]; gM: host [nrhs][6].  Stages src and t0
 // through the context's staging area and waits for the result.
-int grad_moment_launch(Ctx* c, int i_omega, const z128* mu, int nrhs, const int* src, const double* t0, double* gM) {
+int grad_moment_launch(Ctx* c, int i_omega, const z128* muc, int nrhs, const int* src, const double* t0, double* gM) {
     char* st = (char*)c->stage;
     int* dsrc = (int*)st;
     double* dt0 = (double*)(st + 1024);
@@ -873,7 +823,7 @@ int grad_moment_launch(Ctx* c, int i_omega, const z128* mu, int nrhs, const int*
     LS_HIP(hipMemcpyAsync(dsrc, src, 3 * nrhs * sizeof(int), hipMemcpyHostToDevice, c->stream));
     LS_HIP(hipMemcpyAsync(dt0, t0, nrhs * sizeof(double), hipMemcpyHostToDevice, c->stream));
     const double h3 = c->h * c->h * c->h;
-    hipLaunchKernelGGL(k_grad_moment, dim3((unsigned)((nrhs + 63) / 64)), dim3(64), 0, c->stream, mu, dsrc, dt0, dgM,
+    hipLaunchKernelGGL(k_grad_moment, dim3((unsigned)((nrhs + 63) / 64)), dim3(64), 0, c->stream, muc, dsrc, dt0, dgM,
                        nrhs, c->n1, c->n2, c->n3, 1.0 / c->h, c->omega[i_omega], 1.0 / h3);
     LS_HIP(hipGetLastError());
     LS_HIP(hipMemcpyAsync(gM, dgM, 6 * nrhs * sizeof(double), hipMemcpyDeviceToHost, c->stream));

@@ -53,7 +53,8 @@ __device__ __forceinline__ unsigned line_position(long long line, long long lpr)
     return (unsigned)line / (unsigned)lpr;
 }
 
-// MODE 0: in place into data; 1: out = u - v (compact, slot rows); 2: out = v (compact, slot rows)
+// MODE 0: in place into data; 1: out = u - v (compact, slot rows); 2: out = v (compact, slot rows); 3: as 0, but the
+// input lines are rows of the compact field u (slot rows)
 template <typename T, int L, int TY, int SIGN, int MODE>
 __global__ __launch_bounds__(kThreads) void k_fft_contig(cpx<T>* __restrict__ data, long long nlines, int D2,
                                                          long long S1, long long S2, int n_in, int n_out,
@@ -69,8 +70,12 @@ __global__ __launch_bounds__(kThreads) void k_fft_contig(cpx<T>* __restrict__ da
         const long long line = line0 + ln;
         cpx<T> val = {T(0), T(0)};
         if (line < nlines && e < n_in) {
-            const long long o1 = line / D2, o2 = line - o1 * D2;
-            val = data[o1 * S1 + o2 * S2 + e];
+            if constexpr (MODE == 3) {
+                val = u[slot_row(line, lpr, line_position<TY>(line, lpr), sm, D2, zbs) * n_in + e];
+            } else {
+                const long long o1 = line / D2, o2 = line - o1 * D2;
+                val = data[o1 * S1 + o2 * S2 + e];
+            }
         }
         s[e * LDP + ln] = val;
     }
@@ -81,7 +86,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_contig(cpx<T>* __restrict__ da
         const long long line = line0 + ln;
         if (line < nlines && e < n_out) {
             const cpx<T> v = s[e * LDP + ln];
-            if constexpr (MODE == 0) {
+            if constexpr (MODE == 0 || MODE == 3) {
                 const long long o1 = line / D2, o2 = line - o1 * D2;
                 data[o1 * S1 + o2 * S2 + e] = v;
             } else {
@@ -382,8 +387,9 @@ __device__ __forceinline__ void contig_dot_parts(const double acc[3], int tid, d
 template <typename T, int L, int LDP>
 constexpr bool kSwzX = sizeof(T) == 4 && (L == 128 || L == 256 || L == 512) && (LDP - 1) * FourStep<L>::N1 <= L;
 
-// Contiguous (x) pass over TY lines per block.  MODE 0: forward in place; MODE 1: inverse with
-// out = u - v (compact); MODE 2: inverse with out = v (compact).
+// Contiguous (x) pass over TY lines per block.  MODE 0: forward in place; MODE 3: forward, the input lines rows of the
+// compact field u (a copy into the padded buffer first cost 41 us of 880 us per transposed application at 96^3, 3
+// right-hand sides); MODE 1: inverse with out = u - v (compact); MODE 2: inverse with out = v (compact).
 // DOT (MODE 1 only): inner products of the written field, fused for the Bi-CGSTAB iteration that
 // called the operator: 1 = a^H out (slots re, im), 2 = out^H u and ||out||^2 (slots re, im, norm),
 // summed over the block in a fixed order into dot_parts[(rhs kRedSlots + slot) nparts + block of the
@@ -407,16 +413,17 @@ __global__ __launch_bounds__(TY * FourStep<L>::N1) void k_fs_contig(cpx<T>* __re
     stage_twiddles<T, L>(tws, tw, tid, TY * F::N1);
     const long long line = (long long)blockIdx.x * TY + ln;
     const bool valid = line < nlines;
-    // compact output row of this thread's line (MODE 1, 2), computed once
+    // compact row of this thread's line (MODE 1, 2, 3), computed once
     const long long orow = (MODE == 0 || !valid) ? 0 : slot_row(line, lpr, line_position<TY>(line, lpr), sm, D2, zbs);
     const long long o1 = line / D2, o2 = line - o1 * D2;
     cpx<T>* base = data + o1 * S1 + o2 * S2;
     cpx<T> v[F::N2];
-    if constexpr (MODE == 0) {
+    if constexpr (MODE == 0 || MODE == 3) {
+        const cpx<T>* in = MODE == 3 ? u + orow * n_in : base;
 #pragma unroll
         for (int j = 0; j < F::N2; ++j) {
             const int e = q + F::N1 * j;
-            v[j] = (!half_slot<L, PRUNE>(j) && valid && e < n_in) ? base[e] : cpx<T>{T(0), T(0)};
+            v[j] = (!half_slot<L, PRUNE>(j) && valid && e < n_in) ? in[e] : cpx<T>{T(0), T(0)};
         }
         __syncthreads();
         fs_forward<T, L, LDP, SIGN, false, kSwzX<T, L, LDP>>(v, lds, tws, ln, q);
@@ -495,11 +502,12 @@ __global__ __launch_bounds__(TY * 16) void k_fs_contig3(cpx<T>* __restrict__ dat
     const bool s1 = q < A;
     const int qa = s1 ? q : A - 1;
     cpx<T> v[B];
-    if constexpr (MODE == 0) {
+    if constexpr (MODE == 0 || MODE == 3) {
+        const cpx<T>* in = MODE == 3 ? u + orow * n_in : base;
 #pragma unroll
         for (int j = 0; j < B; ++j) {
             const int e = q + A * j;
-            v[j] = (s1 && !(PRUNE && j >= B / 2) && valid && e < n_in) ? base[e] : cpx<T>{T(0), T(0)};
+            v[j] = (s1 && !(PRUNE && j >= B / 2) && valid && e < n_in) ? in[e] : cpx<T>{T(0), T(0)};
         }
         __syncthreads();
         reg_dft<SIGN, B, T, PRUNE>(v);
@@ -584,11 +592,12 @@ __global__ __launch_bounds__(TY * 32) void k_fs_contig3p(cpx<T>* __restrict__ da
     const int k2 = q >> 1;
     const bool h = q & 1;
     cpx<T> v[B];
-    if constexpr (MODE == 0) {
+    if constexpr (MODE == 0 || MODE == 3) {
+        const cpx<T>* in = MODE == 3 ? u + orow * n_in : base;
 #pragma unroll
         for (int j = 0; j < B; ++j) {
             const int e = q + A * j;
-            v[j] = (s1 && !(PRUNE && j >= B / 2) && valid && e < n_in) ? base[e] : cpx<T>{T(0), T(0)};
+            v[j] = (s1 && !(PRUNE && j >= B / 2) && valid && e < n_in) ? in[e] : cpx<T>{T(0), T(0)};
         }
         __syncthreads();
         reg_dft<SIGN, B, T, PRUNE>(v);
@@ -818,7 +827,7 @@ int supported_fft_length(int n) {
 // 4 x inverse with the epilogue) with kernel variant 0 (register four-step) or 1 (LDS Stockham).
 template <typename T>
 int run_pass(Ctx* c, int pass, int variant, const RhsSet& set, cpx<T>* work, const cpx<T>* u, cpx<T>* Au,
-             bool subtract_from_u) {
+             bool subtract_from_u, const cpx<T>* f) {
     const int N1 = c->n1, N2 = c->n2, N3 = c->n3, L1 = c->L1, L2 = c->L2;
     const int nrhs = set.n;
     const long long rc = 3LL * nrhs;
@@ -829,7 +838,11 @@ int run_pass(Ctx* c, int pass, int variant, const RhsSet& set, cpx<T>* work, con
     const int zbs = c->zbs, B = 1 << zbs;
     const long long zblock = plane << zbs;
     switch (pass) {
-        case 0:  // x forward on the N2 x N3 data lines
+        case 0:  // x forward on the N2 x N3 data lines, from work or from the compact field f
+            if (f)
+                return launch_contig<T, -1, 3, true>(c, L1, work, rc * N3 * N2, N2 * B, zblock, L1, N1, L1,
+                                                     twiddles<T>(c, L1), f, nullptr, LS_PNAME(T, "fft_x_fwd"), variant,
+                                                     zbs, slot_map(set), lpr, nrhs);
             return launch_contig<T, -1, 0, true>(c, L1, work, rc * N3 * N2, N2 * B, zblock, L1, N1, L1,
                                                  twiddles<T>(c, L1), nullptr, nullptr, LS_PNAME(T, "fft_x_fwd"), variant,
                                                  zbs, SlotMap{}, 1, nrhs);
@@ -877,10 +890,11 @@ int xy_chunk_rule(const Ctx* c, int nrhs) {
     return (int)std::max(1LL, std::min<long long>(nrhs, kMallBytes / per));
 }
 
-// Au = u - Gconv(f) (subtract_from_u) or Au = Gconv(f), where f already sits in work.  The x and y passes run
+// Au = u - Gconv(f) (subtract_from_u) or Au = Gconv(f), where f already sits in work, or is given compact.  The x and y passes run
 // per chunk of right-hand-side positions (Ctx::xy_chunk, else xy_chunk_rule), the z pass over all of them.
 template <typename T>
-int fft_apply_passes(Ctx* c, const RhsSet& set, cpx<T>* work, const cpx<T>* u, cpx<T>* Au, bool subtract_from_u) {
+int fft_apply_passes(Ctx* c, const RhsSet& set, cpx<T>* work, const cpx<T>* u, cpx<T>* Au, bool subtract_from_u,
+                     const cpx<T>* f) {
     const int prec = sizeof(T) == 8 ? 0 : 1;
     const int ch = c->xy_chunk[prec] > 0 ? std::min(c->xy_chunk[prec], set.n) : xy_chunk_rule<T>(c, set.n);
     const long long pos = 3LL * c->n3 * c->L2 * c->L1;   // work elements per position
@@ -894,14 +908,14 @@ int fft_apply_passes(Ctx* c, const RhsSet& set, cpx<T>* work, const cpx<T>* u, c
     for (int a = 0; a < set.n; a += ch) {
         const RhsSet s_ = chunk(a);
         for (int pass = 0; pass < 2; ++pass)
-            if ((rc_ = run_pass<T>(c, pass, c->variant[prec][pass], s_, work + a * pos, u, Au, subtract_from_u)))
+            if ((rc_ = run_pass<T>(c, pass, c->variant[prec][pass], s_, work + a * pos, u, Au, subtract_from_u, f)))
                 return rc_;
     }
-    if ((rc_ = run_pass<T>(c, 2, c->variant[prec][2], set, work, u, Au, subtract_from_u))) return rc_;
+    if ((rc_ = run_pass<T>(c, 2, c->variant[prec][2], set, work, u, Au, subtract_from_u, f))) return rc_;
     for (int a = 0; a < set.n; a += ch) {
         const RhsSet s_ = chunk(a);
         for (int pass = 3; pass < 5; ++pass)
-            if ((rc_ = run_pass<T>(c, pass, c->variant[prec][pass], s_, work + a * pos, u, Au, subtract_from_u)))
+            if ((rc_ = run_pass<T>(c, pass, c->variant[prec][pass], s_, work + a * pos, u, Au, subtract_from_u, f)))
                 return rc_;
     }
     return LS_OK;
@@ -938,7 +952,7 @@ int autotune_passes(Ctx* c) {
         float best = 0.f;
         for (int variant = 0; variant < 2 && rc_ == LS_OK; ++variant) {
             float ms = 0.f;
-            rc_ = timed([&] { return run_pass<T>(c, pass, variant, set, work, out, out, false); }, ms);
+            rc_ = timed([&] { return run_pass<T>(c, pass, variant, set, work, out, out, false, nullptr); }, ms);
             if (rc_ == LS_OK && (variant == 0 || ms < best)) {
                 best = ms;
                 c->variant[prec][pass] = variant;
@@ -1029,8 +1043,8 @@ int fused_dot_blocks(const Ctx* c) {
 template int fused_dot_blocks<double>(const Ctx*);
 template int fused_dot_blocks<float>(const Ctx*);
 
-template int fft_apply_passes<double>(Ctx*, const RhsSet&, z128*, const z128*, z128*, bool);
-template int fft_apply_passes<float>(Ctx*, const RhsSet&, z64*, const z64*, z64*, bool);
+template int fft_apply_passes<double>(Ctx*, const RhsSet&, z128*, const z128*, z128*, bool, const z128*);
+template int fft_apply_passes<float>(Ctx*, const RhsSet&, z64*, const z64*, z64*, bool, const z64*);
 template int fft_full_3d_forward<double>(Ctx*, z128*);
 
 }  // namespace ls
