@@ -211,14 +211,14 @@ __global__ __launch_bounds__(NT, MINB) void k_contrast_zmarch(
     __shared__ cpx<T> us[4 * 3 * UP];
     __shared__ cpx<T> ts[2 * 6 * SP];
 
-    const long long lb = xcd_logical_block(blockIdx.x, nb_real);
+    const int lb = xcd_logical_block(blockIdx.x, (unsigned)nb_real);
     if (lb < 0) return;
     const int t = threadIdx.x;
-    const int rhs = (int)(lb % nrhs);
-    const long long col = lb / nrhs;
-    const int x0 = (int)(col % tx) * BX;
-    const int y0 = (int)((col / tx) % ty) * BY;
-    const int z0 = (int)(col / ((long long)tx * ty)) * nzc;
+    const unsigned col = (unsigned)lb / (unsigned)nrhs, row = col / (unsigned)tx;
+    const int rhs = (int)((unsigned)lb - col * (unsigned)nrhs);
+    const int x0 = (int)(col - row * (unsigned)tx) * BX;
+    const int y0 = (int)(row % (unsigned)ty) * BY;
+    const int z0 = (int)(row / (unsigned)ty) * nzc;
     const int zend = min(z0 + nzc, N3);
     const long long n = (long long)N1 * N2 * N3;
     const long long plane = (long long)N1 * N2;
@@ -647,13 +647,14 @@ bool use_fused_contrast() {
     return fused;
 }
 
-// z chunk of the fused kernel: blocks run in rounds of (CUs x resident blocks per CU), each block
-// costs its chunk plus about three planes of prologue; pick the chunk (at least 8 planes) that
-// minimises rounds x (chunk + 3).
+// z chunk of the fused kernel: blocks run in rounds of (CUs x resident blocks per CU), each block costs its chunk plus
+// about three planes of prologue; pick the chunk that minimises rounds x (chunk + 3).  Where a grid has fewer blocks than
+// the chip takes, the chunks go down to single planes: a step's latency is all there is (16^3 with chunks of at least 8
+// 25.2 us, now 12.2; 40x33x24, 3 right-hand sides in FP64, 31 -> 20 us).
 inline int fused_z_chunk(int n3, long long cols, long long slots) {
     int best = n3;
     long long best_cost = -1;
-    for (int nzc = std::min(8, n3); nzc <= n3; ++nzc) {
+    for (int nzc = 1; nzc <= n3; ++nzc) {
         const long long nb = cols * ((n3 + nzc - 1) / nzc);
         const long long cost = ((nb + slots - 1) / slots) * (nzc + 3);
         if (best_cost < 0 || cost < best_cost) best = nzc, best_cost = cost;
@@ -661,31 +662,54 @@ inline int fused_z_chunk(int n3, long long cols, long long slots) {
     return best;
 }
 
-// Tile, block size and resident blocks per CU: c64 32x4 cells, 256 threads (128 owned, 72 halo), 47 KB
-// LDS, three blocks per CU; c128 32x8 cells, 384 threads (256 owned, 80 halo), 145 KB LDS, one block.
-template <typename T>
+// Tile, block size and resident blocks per CU.  FP64: 32 x 8 cells, 384 threads (256 owned, 80 halo), 145 KB LDS, one
+// block.  FP32: 32 x 4 cells, 256 threads (128 owned, 72 halo), 47 KB LDS, three blocks; or the narrow tile, 16 x 8
+// cells, 192 threads (48 halo), 40 KB, four blocks.  The narrow one does less halo work and wastes less of grids that are
+// no multiple of 32 wide, but reads half lines; it is the faster where the grid's fields stay in the caches (96^3, 3
+// right-hand sides, 21 entries: 85 against 93 us; 48^3, 6: 27 against 34) and the slower from 128^3 on (142.7 against
+// 148 us with 2 right-hand sides; 256^3 629 against 860).
+template <typename T, bool NARROW>
 struct FusedShape;
 template <>
-struct FusedShape<float> {
-    static constexpr int BX = 32, BY = 4, NT = 256, PER_CU = 3;
+struct FusedShape<float, false> {
+    static constexpr int BX = 32, BY = 4, NT = 256, PER_CU = 3, WAVES = 3;
     static constexpr bool DB = true;
 };
 template <>
-struct FusedShape<double> {
-    static constexpr int BX = 32, BY = 8, NT = 384, PER_CU = 1;
+struct FusedShape<float, true> {
+    static constexpr int BX = 16, BY = 8, NT = 192, PER_CU = 4, WAVES = 3;
+    static constexpr bool DB = true;
+};
+template <>
+struct FusedShape<double, false> {
+    static constexpr int BX = 32, BY = 8, NT = 384, PER_CU = 1, WAVES = 1;
     static constexpr bool DB = false;
 };
 
+// whether the FP32 kernel takes the narrow tile: grids up to a million cells, or a fifth fewer cells in its tiles
 template <typename T>
-size_t packed_elems(const Ctx* c) {
-    using S = FusedShape<T>;
+bool narrow_tile(const Ctx* c) {
+    if (sizeof(T) == 8) return false;
+    auto covered = [&](int bx, int by) { return (long long)((c->n1 + bx - 1) / bx * bx) * ((c->n2 + by - 1) / by * by); };
+    return c->ncell <= 1000000 || covered(16, 8) * 5 < covered(32, 4) * 4;
+}
+
+template <typename T, bool NARROW>
+size_t packed_elems_of(const Ctx* c) {
+    using S = FusedShape<T, NARROW>;
     const size_t tx = (c->n1 + S::BX - 1) / S::BX, ty = (c->n2 + S::BY - 1) / S::BY;
     return tx * ty * (size_t)c->n3 * 21 * S::BX * S::BY;
 }
-
 template <typename T>
-int pack_contrast(Ctx* c, T* dst) {
-    using S = FusedShape<T>;
+size_t packed_elems(const Ctx* c) {
+    if constexpr (sizeof(T) == 4)
+        if (narrow_tile<T>(c)) return packed_elems_of<T, true>(c);
+    return packed_elems_of<T, false>(c);
+}
+
+template <typename T, bool NARROW>
+int pack_contrast_tiles(Ctx* c, T* dst) {
+    using S = FusedShape<T, NARROW>;
     LS_HIP(hipMemsetAsync(dst, 0, packed_elems<T>(c) * sizeof(T), c->stream));
     const long long n = c->ncell;
     const dim3 g((unsigned)((n + 255) / 256));
@@ -696,6 +720,12 @@ int pack_contrast(Ctx* c, T* dst) {
                            c->n3);
     LS_HIP(hipGetLastError());
     return LS_OK;
+}
+template <typename T>
+int pack_contrast(Ctx* c, T* dst) {
+    if constexpr (sizeof(T) == 4)
+        if (narrow_tile<T>(c)) return pack_contrast_tiles<T, true>(c, dst);
+    return pack_contrast_tiles<T, false>(c, dst);
 }
 
 // values per cell of the packed contrast: 9 if the folded contrast has the orthotropic pattern at every cell,
@@ -729,9 +759,9 @@ SlotW2<T> slot_w2(const Ctx* c, const RhsSet& set) {
     return sw;
 }
 
-template <typename T, int OUT>
-int launch_fused(Ctx* c, const RhsSet& set, const cpx<T>* u, cpx<T>* out, const cpx<T>* y) {
-    using S = FusedShape<T>;
+template <typename T, int OUT, bool NARROW>
+int launch_fused_tiles(Ctx* c, const RhsSet& set, const cpx<T>* u, cpx<T>* out, const cpx<T>* y) {
+    using S = FusedShape<T, NARROW>;
     const int nrhs = set.n;
     const int tx = (c->n1 + S::BX - 1) / S::BX, ty = (c->n2 + S::BY - 1) / S::BY;
     const long long cols = (long long)tx * ty * nrhs;
@@ -740,16 +770,23 @@ int launch_fused(Ctx* c, const RhsSet& set, const cpx<T>* u, cpx<T>* out, const 
     const unsigned nbl = (unsigned)((nb + 7) / 8 * 8);
     c->prof.begin(c->stream, OUT == 0 ? LS_PNAME(T, "contrast_fused") : LS_PNAME(T, "contrast_fused_T"), nrhs);
     if (c->contrast_k == 9)
-        hipLaunchKernelGGL((k_contrast_zmarch<T, S::BX, S::BY, S::NT, S::PER_CU, S::DB, OUT, 9>), dim3(nbl), dim3(S::NT), 0,
+        hipLaunchKernelGGL((k_contrast_zmarch<T, S::BX, S::BY, S::NT, S::WAVES, S::DB, OUT, 9>), dim3(nbl), dim3(S::NT), 0,
                            c->stream, u, contrast_packed_of<T>(c), density_of<T>(c), out, y, slot_w2<T>(c, set), nrhs, c->n1,
                            c->n2, c->n3, c->L1, c->L2, T(1.0 / c->h), tx, ty, nzc, nb, c->zbs);
     else
-        hipLaunchKernelGGL((k_contrast_zmarch<T, S::BX, S::BY, S::NT, S::PER_CU, S::DB, OUT, 21>), dim3(nbl), dim3(S::NT), 0,
+        hipLaunchKernelGGL((k_contrast_zmarch<T, S::BX, S::BY, S::NT, S::WAVES, S::DB, OUT, 21>), dim3(nbl), dim3(S::NT), 0,
                            c->stream, u, contrast_packed_of<T>(c), density_of<T>(c), out, y, slot_w2<T>(c, set), nrhs, c->n1,
                            c->n2, c->n3, c->L1, c->L2, T(1.0 / c->h), tx, ty, nzc, nb, c->zbs);
     c->prof.end(c->stream);
     LS_HIP(hipGetLastError());
     return LS_OK;
+}
+
+template <typename T, int OUT>
+int launch_fused(Ctx* c, const RhsSet& set, const cpx<T>* u, cpx<T>* out, const cpx<T>* y) {
+    if constexpr (sizeof(T) == 4)
+        if (narrow_tile<T>(c)) return launch_fused_tiles<T, OUT, true>(c, set, u, out, y);
+    return launch_fused_tiles<T, OUT, false>(c, set, u, out, y);
 }
 
 template <typename T>
