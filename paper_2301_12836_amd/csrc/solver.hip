@@ -42,26 +42,29 @@ enum {
     S_DONE = 15      // 1: converged
 };
 
-__device__ __forceinline__ double2 block_reduce2(double a, double b, double* sh) {
-    const int tid = threadIdx.x;
-    sh[tid] = a;
-    sh[kThreads + tid] = b;
-    __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if (tid < w) {
-            sh[tid] += sh[tid + w];
-            sh[kThreads + tid] += sh[kThreads + tid + w];
-        }
-        __syncthreads();
-    }
-    return make_double2(sh[0], sh[kThreads]);
+// sums of a and b over the block in a fixed order (wavefront shuffles, then the wavefronts in order) into the block's
+// partials of slots `slot` and `slot` + 1; sh: kPartSh doubles, a region for each slot, so that a block may write several
+// pairs one after the other
+constexpr int kWaves = kThreads / 64, kPartSh = kRedSlots * kWaves;
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    return v;
 }
 
 __device__ __forceinline__ void write_partials(double* partials, int r, int slot, double a, double b, double* sh) {
-    const double2 s = block_reduce2(a, b, sh);
-    if (threadIdx.x == 0) {
-        partials[((long long)r * kRedSlots + slot) * kRedBlocks + blockIdx.x] = s.x;
-        partials[((long long)r * kRedSlots + slot + 1) * kRedBlocks + blockIdx.x] = s.y;
+    a = wave_sum(a);
+    b = wave_sum(b);
+    sh += slot * kWaves;
+    if ((threadIdx.x & 63) == 0) {
+        sh[threadIdx.x >> 6] = a;
+        sh[kWaves + (threadIdx.x >> 6)] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double v = 0.0;
+        for (int w = 0; w < kWaves; ++w) v += sh[threadIdx.x * kWaves + w];
+        partials[((long long)r * kRedSlots + slot + threadIdx.x) * kRedBlocks + blockIdx.x] = v;
     }
 }
 
@@ -82,7 +85,7 @@ __global__ __launch_bounds__(kThreads) void k_init(const cpx<T>* __restrict__ b,
                                                    cpx<T>* __restrict__ r, cpx<T>* __restrict__ rhat,
                                                    cpx<T>* __restrict__ p, cpx<T>* __restrict__ v, long long m,
                                                    double* partials, SlotMap sm) {
-    __shared__ double sh[2 * kThreads];
+    __shared__ double sh[kPartSh];
     const int rr = sm.slot[blockIdx.y];
     const long long off = (long long)rr * m;
     double bb = 0, nr = 0;
@@ -121,7 +124,7 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_dot(const cpx<T>* __restrict__ a, const cpx<T>* __restrict__ b,
                                                   long long m, const double* __restrict__ state, double* partials,
                                                   SlotMap sm) {
-    __shared__ double sh[2 * kThreads];
+    __shared__ double sh[kPartSh];
     const int rr = sm.slot[blockIdx.y];
     if (state[rr * kStateLen + S_ACTIVE] == 0.0) return;
     const long long off = (long long)rr * m;
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(kThreads) void k_update_s(const cpx<T>* __restrict_
                                                        cpx<T>* __restrict__ s, long long m,
                                                        const double* __restrict__ state, double* partials,
                                                        SlotMap sm) {
-    __shared__ double sh[2 * kThreads];
+    __shared__ double sh[kPartSh];
     const int rr = sm.slot[blockIdx.y];
     const double* st = state + rr * kStateLen;
     if (st[S_ACTIVE] == 0.0) return;
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(kThreads) void k_update_s_pre(const cpx<T>* __restr
                                                            cpx<T>* __restrict__ s, cpx<T>* __restrict__ sh,
                                                            long long n, const double* __restrict__ state,
                                                            double* partials, SlotMap sm, PreTabs<T> pt) {
-    __shared__ double shm[2 * kThreads];
+    __shared__ double shm[kPartSh];
     const int rr = sm.slot[blockIdx.y];
     const double* st = state + rr * kStateLen;
     if (st[S_ACTIVE] == 0.0) return;
@@ -229,27 +232,12 @@ __global__ __launch_bounds__(kThreads) void k_update_s_pre(const cpx<T>* __restr
     write_partials(partials, rr, 0, ss, 0.0, shm);
 }
 
-// x += alpha p for the systems that converged at the half step
-template <typename T, typename X>
-__global__ __launch_bounds__(kThreads) void k_update_x_half(cpx<X>* __restrict__ x, const cpx<T>* __restrict__ p,
-                                                            long long m, double* __restrict__ state, SlotMap sm) {
-    const int rr = sm.slot[blockIdx.y];
-    const double* st = state + rr * kStateLen;
-    if (st[S_FLAG] != 1.0) return;
-    const cpx<X> al = {(X)st[S_ALPHA], (X)st[S_ALPHA + 1]};
-    const long long off = (long long)rr * m;
-    LS_FOR_ELEMS(m) {
-        const cpx<T> pv = p[off + e];
-        x[off + e] = x[off + e] + al * cpx<X>{(X)pv.x, (X)pv.y};
-    }
-}
-
 // partials: t^H s (complex), t^H t
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_dot_ts(const cpx<T>* __restrict__ t, const cpx<T>* __restrict__ s,
                                                      long long m, const double* __restrict__ state,
                                                      double* partials, SlotMap sm) {
-    __shared__ double sh[2 * kThreads];
+    __shared__ double sh[kPartSh];
     const int rr = sm.slot[blockIdx.y];
     if (state[rr * kStateLen + S_ACTIVE] == 0.0) return;
     const long long off = (long long)rr * m;
@@ -265,7 +253,8 @@ __global__ __launch_bounds__(kThreads) void k_dot_ts(const cpx<T>* __restrict__ 
     write_partials(partials, rr, 2, tt, 0.0, sh);
 }
 
-// x += alpha p + omega s; r = s - omega t; partials ||r||^2, r^H r (complex)
+// x += alpha p + omega s; r = s - omega t; partials ||r||^2, r^H r (complex); only x += alpha p for the systems that
+// converged at the half step
 // PRE: the x step takes xs (M^-1 s) instead of s
 template <typename T, typename X, bool PRE>
 __global__ __launch_bounds__(kThreads) void k_update_xr(cpx<X>* __restrict__ x, const cpx<T>* __restrict__ p,
@@ -274,14 +263,22 @@ __global__ __launch_bounds__(kThreads) void k_update_xr(cpx<X>* __restrict__ x, 
                                                         const cpx<T>* __restrict__ rhat, long long m,
                                                         const double* __restrict__ state, double* partials,
                                                         SlotMap sm) {
-    __shared__ double sh[2 * kThreads];
+    __shared__ double sh[kPartSh];
     const int rr = sm.slot[blockIdx.y];
     const double* st = state + rr * kStateLen;
-    if (st[S_ACTIVE] == 0.0) return;
     const cpx<X> alx = {(X)st[S_ALPHA], (X)st[S_ALPHA + 1]};
+    const long long off = (long long)rr * m;
+    if (st[S_ACTIVE] == 0.0) {
+        if (st[S_FLAG] == 1.0) {
+            LS_FOR_ELEMS(m) {
+                const cpx<T> pv = p[off + e];
+                x[off + e] = x[off + e] + alx * cpx<X>{(X)pv.x, (X)pv.y};
+            }
+        }
+        return;
+    }
     const cpx<X> omx = {(X)st[S_OMEGA], (X)st[S_OMEGA + 1]};
     const cpx<T> om = {(T)st[S_OMEGA], (T)st[S_OMEGA + 1]};
-    const long long off = (long long)rr * m;
     double nr = 0, re = 0, im = 0;
     LS_FOR_ELEMS(m) {
         const cpx<T> pv = load_nt(&p[off + e]), sv = load_nt(&s[off + e]);
@@ -304,7 +301,7 @@ __global__ __launch_bounds__(kThreads) void k_update_xr(cpx<X>* __restrict__ x, 
 __global__ __launch_bounds__(kThreads) void k_residual(const z128* __restrict__ b, const z128* __restrict__ ax,
                                                        z128* __restrict__ r, long long m, double* partials,
                                                        SlotMap sm) {
-    __shared__ double sh[2 * kThreads];
+    __shared__ double sh[kPartSh];
     const int rr = sm.slot[blockIdx.y];
     const long long off = (long long)rr * m;
     double nr = 0, bb = 0;
@@ -350,7 +347,9 @@ __global__ void k_copy(const z128* __restrict__ a, z128* __restrict__ b, long lo
     LS_FOR_ELEMS(m) { b[off + e] = a[off + e]; }
 }
 
-// Sum the kRedBlocks partials of each slot in a fixed order, then advance the scalars.
+// Sum the partials of each slot in a fixed order, then advance the scalars.  One block on the serial chain of an
+// iteration, so latency bound: the state is read with the partials, the sums go through shuffles and one barrier.
+// 5.6 -> 3.8 us a call at 16^3, two or four of which stand in every iteration.
 enum Phase { PH_INIT = 0, PH_ALPHA = 1, PH_S = 2, PH_OMEGA = 3, PH_RHO = 4, PH_RESID = 5 };
 
 // partials: [rhs][kRedSlots][nparts] (nparts = kRedBlocks, or the x-inverse epilogue's blocks per right-hand
@@ -360,25 +359,43 @@ __global__ __launch_bounds__(kThreads) void k_finalize(const double* __restrict_
                                                        double* __restrict__ state, int phase, int nslots, double tol2,
                                                        double* __restrict__ out, const double* __restrict__ tol2v,
                                                        SlotMap sm) {
-    __shared__ double sh[kRedSlots][kThreads];
+    __shared__ double sh[kWaves][kRedSlots], st0[kStateLen];
     const int rr = sm.slot[blockIdx.x];
     double* st = state + rr * kStateLen;
     const int tid = threadIdx.x;
-    if (phase != PH_INIT && phase != PH_RESID && st[S_ACTIVE] == 0.0) return;
-    for (int q = 0; q < nslots; ++q) {
-        double a = 0;
-        for (int k = tid; k < nparts; k += kThreads) a += partials[((long long)rr * kRedSlots + q) * nparts + k];
-        sh[q][tid] = a;
+    if (tid < kStateLen) st0[tid] = st[tid];
+    double v[kRedSlots] = {};
+    // kAhead strides at once, over every slot (the last again where there are fewer): their loads go out together
+    constexpr int kAhead = 4;
+    for (int k = tid; k < nparts; k += kAhead * kThreads) {
+        double a[kRedSlots][kAhead];
+#pragma unroll
+        for (int q = 0; q < kRedSlots; ++q)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+                a[q][i] = partials[((long long)rr * kRedSlots + min(q, nslots - 1)) * nparts +
+                                   min(k + i * kThreads, nparts - 1)];
+#pragma unroll
+        for (int q = 0; q < kRedSlots; ++q)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) v[q] += k + i * kThreads < nparts ? a[q][i] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < kRedSlots; ++q) {
+        v[q] = wave_sum(v[q]);
+        if ((tid & 63) == 0) sh[tid >> 6][q] = v[q];
     }
     __syncthreads();
-    for (int w = kThreads / 2; w > 0; w >>= 1) {
-        if (tid < w)
-            for (int q = 0; q < nslots; ++q) sh[q][tid] += sh[q][tid + w];
-        __syncthreads();
-    }
     if (tid != 0) return;
-    double v[kRedSlots];
-    for (int q = 0; q < nslots; ++q) v[q] = sh[q][0];
+    if (phase != PH_INIT && phase != PH_RESID && st0[S_ACTIVE] == 0.0) {
+        if (phase == PH_RHO && st0[S_FLAG] == 1.0) st[S_FLAG] = 0.0;   // its x += alpha p is done
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < kRedSlots; ++q) {
+        v[q] = 0.0;
+        for (int w = 0; w < kWaves; ++w) v[q] += sh[w][q];
+    }
     auto bad = [](double x) { return !(fabs(x) <= 1.7e308); };
     switch (phase) {
         case PH_INIT: {  // v = (||b||^2, ||r||^2)
@@ -408,13 +425,13 @@ __global__ __launch_bounds__(kThreads) void k_finalize(const double* __restrict_
         case PH_ALPHA: {  // v = r^H v
             const double dr = v[0], di = v[1];
             const double den = dr * dr + di * di;
-            st[S_ITERS] += 1.0;
+            st[S_ITERS] = st0[S_ITERS] + 1.0;
             if (!(den > 0.0) || bad(den)) {
                 st[S_FLAG] = bad(den) ? 3.0 : 2.0;
                 st[S_ACTIVE] = 0.0;
                 break;
             }
-            const double rr_ = st[S_RHO], ri = st[S_RHO + 1];
+            const double rr_ = st0[S_RHO], ri = st0[S_RHO + 1];
             st[S_ALPHA] = (rr_ * dr + ri * di) / den;
             st[S_ALPHA + 1] = (ri * dr - rr_ * di) / den;
             break;
@@ -424,7 +441,7 @@ __global__ __launch_bounds__(kThreads) void k_finalize(const double* __restrict_
             if (bad(v[0])) {
                 st[S_FLAG] = 3.0;
                 st[S_ACTIVE] = 0.0;
-            } else if (v[0] <= st[S_TOL2]) {
+            } else if (v[0] <= st0[S_TOL2]) {
                 st[S_FLAG] = 1.0;
                 st[S_ACTIVE] = 0.0;
                 st[S_DONE] = 1.0;
@@ -451,15 +468,15 @@ __global__ __launch_bounds__(kThreads) void k_finalize(const double* __restrict_
                 st[S_ACTIVE] = 0.0;
                 break;
             }
-            if (v[0] <= st[S_TOL2]) {
+            if (v[0] <= st0[S_TOL2]) {
                 st[S_ACTIVE] = 0.0;
                 st[S_DONE] = 1.0;
                 break;
             }
             // beta = (rho_new / rho)(alpha / omega)
-            const double pr = st[S_RHO], pi = st[S_RHO + 1];
-            const double ar = st[S_ALPHA], ai = st[S_ALPHA + 1];
-            const double orr = st[S_OMEGA], oi = st[S_OMEGA + 1];
+            const double pr = st0[S_RHO], pi = st0[S_RHO + 1];
+            const double ar = st0[S_ALPHA], ai = st0[S_ALPHA + 1];
+            const double orr = st0[S_OMEGA], oi = st0[S_OMEGA + 1];
             const double d1 = pr * pr + pi * pi, d2 = orr * orr + oi * oi;
             if (!(d1 > 0.0) || !(d2 > 0.0) || !(nr * nr + ni * ni > 0.0)) {
                 st[S_FLAG] = 2.0;
@@ -480,12 +497,6 @@ __global__ __launch_bounds__(kThreads) void k_finalize(const double* __restrict_
             break;
         }
     }
-}
-
-__global__ void k_clear_half(double* state, int n, SlotMap sm) {
-    if ((int)threadIdx.x >= n) return;
-    const int rr = sm.slot[threadIdx.x];
-    if (state[rr * kStateLen + S_FLAG] == 1.0) state[rr * kStateLen + S_FLAG] = 0.0;
 }
 
 struct Vecs64 {
@@ -635,8 +646,6 @@ int bicgstab(Ctx* c, const RhsSet& all, const cpx<T>* b, cpx<X>* x, const cpx<T>
                                sm);
         c->prof.end(c->stream);
         if ((brc = finalize(c, cur, PH_S, 1))) return brc;
-        hipLaunchKernelGGL((k_update_x_half<T, X>), g, dim3(kThreads), 0, c->stream, x, pre ? ph : p, m, c->state, sm);
-        hipLaunchKernelGGL(k_clear_half, dim3(1), dim3(kMaxRhs), 0, c->stream, c->state, cur.n, sm);
         if (fblocks) c->dot = {2, nullptr, c->dparts, flines, fblocks};
         brc = apply(cur, pre ? sh : s, t);
         c->dot = {};
@@ -767,19 +776,18 @@ struct VecSet {
 // wavefronts in order) into gp[(rr kGramSlots + q) kRedBlocks + block]
 template <int NQ>
 __device__ __forceinline__ void block_partials(const double (&a)[NQ], int nq, double* gp, int rr) {
-    __shared__ double sh[kThreads / 64][NQ];
+    __shared__ double sh[kWaves][NQ];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         if (q >= nq) break;
-        double v = a[q];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+        const double v = wave_sum(a[q]);
         if (lane == 0) sh[wave][q] = v;
     }
     __syncthreads();
     if (threadIdx.x < nq) {
         double v = 0.0;
-        for (int w = 0; w < kThreads / 64; ++w) v += sh[w][threadIdx.x];
+        for (int w = 0; w < kWaves; ++w) v += sh[w][threadIdx.x];
         gp[((long long)rr * kGramSlots + threadIdx.x) * kRedBlocks + blockIdx.x] = v;
     }
 }
@@ -895,23 +903,20 @@ __global__ __launch_bounds__(kThreads) void k_mr(VecSet<T> R, VecSet<T> U, cpx<X
     }
 }
 
-// sums of the first nq partial slots of each right-hand side, in a fixed order -> out[rr kGramSlots + q]
-__global__ __launch_bounds__(kThreads) void k_reduce_slots(const double* __restrict__ gp, int nq,
-                                                           double* __restrict__ out) {
-    __shared__ double sh[kThreads];
-    const int rr = blockIdx.x, tid = threadIdx.x;
-    for (int q = 0; q < nq; ++q) {
-        double a = 0.0;
-        for (int k = tid; k < kRedBlocks; k += kThreads) a += gp[((long long)rr * kGramSlots + q) * kRedBlocks + k];
-        sh[tid] = a;
-        __syncthreads();
-        for (int w = kThreads / 2; w > 0; w >>= 1) {
-            if (tid < w) sh[tid] += sh[tid + w];
-            __syncthreads();
-        }
-        if (tid == 0) out[rr * kGramSlots + q] = sh[0];
-        __syncthreads();
-    }
+// sums of the first nq partial slots of each right-hand side, in a fixed order -> out[rr kGramSlots + q]: a block a slot,
+// since the host waits for them
+__global__ __launch_bounds__(kThreads) void k_reduce_slots(const double* __restrict__ gp, double* __restrict__ out) {
+    __shared__ double sh[kWaves];
+    const int rr = blockIdx.y, q = blockIdx.x, tid = threadIdx.x;
+    double a = 0.0;
+    for (int k = tid; k < kRedBlocks; k += kThreads) a += gp[((long long)rr * kGramSlots + q) * kRedBlocks + k];
+    a = wave_sum(a);
+    if ((tid & 63) == 0) sh[tid >> 6] = a;
+    __syncthreads();
+    if (tid != 0) return;
+    a = 0.0;
+    for (int w = 0; w < kWaves; ++w) a += sh[w];
+    out[rr * kGramSlots + q] = a;
 }
 
 struct LState {
@@ -1025,7 +1030,7 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
         return LS_OK;
     };
     auto reduce = [&](int nq) -> int {
-        hipLaunchKernelGGL(k_reduce_slots, dim3(nrhs), dim3(kThreads), 0, c->stream, c->gpart, nq, out);
+        hipLaunchKernelGGL(k_reduce_slots, dim3(nq, nrhs), dim3(kThreads), 0, c->stream, c->gpart, out);
         LS_HIP(hipGetLastError());
         LS_HIP(hipMemcpyAsync(c->red_host, out, sizeof(double) * nrhs * kGramSlots, hipMemcpyDeviceToHost, c->stream));
         LS_HIP(hipStreamSynchronize(c->stream));
