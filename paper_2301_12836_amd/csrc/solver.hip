@@ -1041,6 +1041,13 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
             if (q.active) return true;
         return false;
     };
+    // the operator over the systems still iterating, as the vector updates
+    auto apply_live = [&](const cpx<T>* in, cpx<T>* to) -> int {
+        RhsSet live;
+        for (int q = 0; q < nrhs; ++q)
+            if (st[q].active) live.slot[live.n++] = q;
+        return apply(live, in, to);
+    };
     int save_rc = LS_OK;
     auto record = [&](int q, double r2) {
         st[q].rnorm2 = r2;
@@ -1113,7 +1120,7 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
             hipLaunchKernelGGL((k_bicg_u<T>), g, dim3(kThreads), 0, c->stream, R, U, j, m, coef);
             c->prof.end(c->stream);
             LS_HIP(hipGetLastError());
-            if ((rc = apply(U.v[j], U.v[j + 1]))) return rc;
+            if ((rc = apply_live(U.v[j], U.v[j + 1]))) return rc;
             for (auto& q : st)
                 if (q.active) q.matvecs += 1;
             // alpha = rho0 / (rhat^H u_{j+1})
@@ -1149,7 +1156,7 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
             }
             if (!any_active()) break;
             // r_{j+1} = A r_j
-            if ((rc = apply(R.v[j], R.v[j + 1]))) return rc;
+            if ((rc = apply_live(R.v[j], R.v[j + 1]))) return rc;
             for (auto& q : st)
                 if (q.active) q.matvecs += 1;
         }
@@ -1323,11 +1330,14 @@ int solve_systems(Ctx* c, const int* freq, const z128* b, int nrhs, double tol, 
     // block-Jacobi right preconditioning: M^-1 (1), or M^-T for the transposed operator (2)
     const int pre = c->precond == LS_PRECOND_BLOCK_JACOBI ? (transposed ? 2 : 1) : 0;
     if (precision == LS_PREC_C128 && c->bicgstab_l > 1) {
-        auto apply = [&](const z128* in, z128* out) { return op_apply<double>(c, all, in, out, transposed); };
+        auto apply = [&](RhsSet set, const z128* in, z128* out) {
+            for (int q = 0; q < set.n; ++q) set.freq[q] = freq[set.slot[q]];
+            return op_apply<double>(c, set, in, out, transposed);
+        };
         const std::vector<z128*> vec = krylov_vectors<double>(c);
         const z128* ax0 = nullptr;
         if (x0) {
-            if ((rc = apply(u_out, vec[1]))) return rc;   // r_1's vector is free until the first cycle
+            if ((rc = apply(all, u_out, vec[1]))) return rc;   // r_1's vector is free until the first cycle
             ax0 = vec[1];
         }
         std::vector<LState> ls;
@@ -1503,7 +1513,10 @@ int solve_systems(Ctx* c, const int* freq, const z128* b, int nrhs, double tol, 
                 hipLaunchKernelGGL(k_to32, gall, dim3(kThreads), 0, c->stream, c->r, c->b32, m, dscale, c->x32,
                                    slot_map(all));
                 LS_HIP(hipGetLastError());
-                auto apply32 = [&](const z64* in, z64* out) { return op_apply<float>(c, all, in, out, transposed); };
+                auto apply32 = [&](RhsSet set, const z64* in, z64* out) {
+                    for (int q = 0; q < set.n; ++q) set.freq[q] = freq[set.slot[q]];
+                    return op_apply<float>(c, set, in, out, transposed);
+                };
                 const std::vector<z64*> vec = krylov_vectors<float>(c);
                 std::vector<LState> ls;
                 double worst = 0.0;
