@@ -349,7 +349,7 @@ __global__ void k_copy(const z128* __restrict__ a, z128* __restrict__ b, long lo
 
 // Sum the partials of each slot in a fixed order, then advance the scalars.  One block on the serial chain of an
 // iteration, so latency bound: the state is read with the partials, the sums go through shuffles and one barrier.
-// 5.6 -> 3.8 us a call at 16^3, two or four of which stand in every iteration.
+// 5.6 -> 2.9-3.8 us a call at 16^3 (two traces); four stand in every iteration.
 enum Phase { PH_INIT = 0, PH_ALPHA = 1, PH_S = 2, PH_OMEGA = 3, PH_RHO = 4, PH_RESID = 5 };
 
 // partials: [rhs][kRedSlots][nparts] (nparts = kRedBlocks, or the x-inverse epilogue's blocks per right-hand
