@@ -152,7 +152,8 @@ typedef struct ls_ctx ls_ctx;
  *           Both are copied; the caller may free them after the call returns.
  *   omega   host, n_omega angular frequencies (rad/s, > 0).
  *   opt     may be NULL (c128, exact Green's tensor, max_rhs 1).
- *   stream  a hipStream_t (NULL = the null stream); all work of this context runs on it.
+ *   stream  a hipStream_t; all work of this context runs on it.  NULL: a private stream, ordered with the null
+ *           stream and, as ls_stream says, with other contexts set up on NULL.
  * Allocates all device memory the context will use (tables, contrast, workspaces).
  * Synchronises the stream before returning.  On error *out is NULL. */
 int ls_setup(const ls_grid* grid, const double C0[36], double rho0,
@@ -186,7 +187,8 @@ int ls_apply(ls_ctx* ctx, int i_omega, const void* u, void* Au, int n_rhs);
  * n_rhs x 3 N3 L2 L1 x 16 bytes (L_a the smallest 2^a or 3 2^a, at least 16, not below 2 N_a - 1: 50 MB for
  * one 64^3 field) must fit in the 64 MiB, else LS_ERR_ARG.  Allocates nothing and clears nothing (every value of the buffer that is read
  * was written earlier in the same call).  Every call on a GPU uses that GPU's one array, so calls that
- * overlap in time on one GPU (different streams or host threads) race; serialise them.  Asynchronous. */
+ * overlap in time on one GPU (different streams or host threads) race; serialise them (contexts set up on the null
+ * stream are, among themselves).  Asynchronous. */
 int ls_apply_noalloc(ls_ctx* ctx, int i_omega, const void* u, void* Au, int n_rhs);
 
 /* The same matvec with the operator, its FFTs and Green's multiply in FP32 (c64 fields; u and Au must
@@ -367,9 +369,9 @@ int ls_kernel_schedule(const ls_ctx* ctx, int* schedule);
 int ls_contrast_format(const ls_ctx* ctx);
 
 /* The hipStream_t the context's work runs on: the one it was set up with or, set up on the null stream, a private
- * blocking stream (ordered with the null stream, not with other contexts' private streams).  A stream-ordered
- * allocator that takes the outputs of asynchronous calls from this stream's pool hands the memory of a dropped
- * output only to later work of the same context.  NULL for a null context. */
+ * blocking stream.  That one is ordered with the null stream, and with the private stream of another context as far as
+ * their calls touch the same memory: a call waits on the device for earlier calls of other such contexts that write what
+ * it reads or writes, or read what it writes.  NULL for a null context. */
 void* ls_stream(const ls_ctx* ctx);
 
 /* Message of the last error on this host thread ("" if none). */

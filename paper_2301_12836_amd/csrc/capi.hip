@@ -9,6 +9,7 @@
 #include <cstring>
 #include <sys/stat.h>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -118,7 +119,7 @@ static void release(Ctx* c) {
     for (auto q : c->tw128) (void)hipFree(q);
     for (auto q : c->tw64) (void)hipFree(q);
     if (c->red_host) (void)hipHostFree(c->red_host);
-    if (c->own_stream) (void)hipStreamDestroy(c->own_stream);
+    private_stream_release(c);
     delete static_cast<ls_ctx*>(c);
 }
 
@@ -232,6 +233,14 @@ int check_cell(const ls_ctx* c, const int* cell) {
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
     return na > 0 && nb > 0 && x < y + nb && y < x + na;
+}
+
+// n_rhs fields of elem bytes per complex value that a call reads (none where null) or writes
+Span reads(const ls_ctx* c, const void* p, int n_rhs, size_t elem = sizeof(z128)) {
+    return {p, p ? (size_t)n_rhs * c->field_elems() * elem : 0, false};
+}
+Span writes(const ls_ctx* c, const void* p, int n_rhs, size_t elem = sizeof(z128)) {
+    return {p, (size_t)n_rhs * c->field_elems() * elem, true};
 }
 
 // in and out of a field-to-field call (n_rhs fields of elem bytes per complex value) must be disjoint
@@ -357,6 +366,15 @@ int check_moment(const ls_ctx* c, int i_omega, const double M[6], const int src[
     for (int J = 0; J < 6; ++J)
         if (!std::isfinite(M[J])) return fail(LS_ERR_ARG, "non-finite moment tensor");
     if (!std::isfinite(t0)) return fail(LS_ERR_ARG, "non-finite rupture time");
+    return LS_OK;
+}
+
+int check_force(const ls_ctx* c, int i_omega, const double F[3], const int cell[3]) {
+    int rc;
+    if ((rc = check_ctx(c)) || (rc = check_omega(c, i_omega)) || (rc = check_cell(c, cell))) return rc;
+    if (!F) return fail(LS_ERR_ARG, "null argument");
+    for (int a = 0; a < 3; ++a)
+        if (!std::isfinite(F[a])) return fail(LS_ERR_ARG, "non-finite force");
     return LS_OK;
 }
 
@@ -535,12 +553,18 @@ int ls_setup(const ls_grid* grid, const double C0[36], double rho0, const double
     if (!c->stream) {
         // the legacy null stream cannot be captured into graphs: work on a private blocking stream,
         // which the runtime keeps ordered with the caller's work on the null stream
-        if (hipStreamCreate(&c->own_stream) != hipSuccess) {
-            (void)hipGetLastError();
-            delete static_cast<ls_ctx*>(c);
-            return fail(LS_ERR_HIP, "stream creation failed");
+        if (private_stream(c) != LS_OK) {
+            const std::string msg = g_last_error;
+            release(c);
+            return fail(LS_ERR_HIP, msg);
         }
-        c->stream = c->own_stream;
+    }
+    const size_t medium = (size_t)c->n1 * c->n2 * c->n3 * sizeof(double);
+    const Span read_medium[] = {{dC, 21 * medium, false}, {drho, medium, false}};
+    if (order_begin_waiting(c, read_medium, 2) != LS_OK) {   // until the end of the call, or its release
+        const std::string msg = g_last_error;
+        release(c);
+        return fail(LS_ERR_HIP, msg);
     }
 
     const size_t n = (size_t)c->ncell;
@@ -659,6 +683,7 @@ int ls_setup(const ls_grid* grid, const double C0[36], double rho0, const double
         g_last_error = msg;
         return rc;
     }
+    order_end_waiting(c);
     *out = static_cast<ls_ctx*>(c);
     return LS_OK;
 }
@@ -669,6 +694,9 @@ int ls_set_contrast(ls_ctx* c, const double* dC, const double* drho) {
     int rc;
     if ((rc = check_ctx(c))) return rc;
     if (!dC || !drho) return fail(LS_ERR_ARG, "null argument");
+    const size_t medium = (size_t)c->ncell * sizeof(double);
+    const WaitingCall call(c, {{dC, 21 * medium, false}, {drho, medium, false}});
+    if (call.rc) return call.rc;
     if ((rc = fold_background(c, dC, drho, c->fold21))) return rc;
     return build_block_jacobi(c);
 }
@@ -678,6 +706,7 @@ int ls_precond_blocks(ls_ctx* c, int i_omega, void* minv) {
     if ((rc = check_ctx(c)) || (rc = check_omega(c, i_omega))) return rc;
     if (!minv) return fail(LS_ERR_ARG, "null argument");
     if (c->precond != LS_PRECOND_BLOCK_JACOBI) return fail(LS_ERR_STATE, "the context has no block-Jacobi preconditioner");
+    if ((rc = order_begin(c, {{minv, 9 * (size_t)c->ncell * sizeof(z128), true}}))) return rc;
     LS_HIP(hipMemcpyAsync(minv, c->minv[i_omega], 9 * (size_t)c->ncell * sizeof(z128), hipMemcpyDeviceToDevice,
                           c->stream));
     return LS_OK;
@@ -689,6 +718,7 @@ int ls_apply(ls_ctx* c, int i_omega, const void* u, void* Au, int n_rhs) {
     if (!u || !Au) return fail(LS_ERR_ARG, "null field pointer");
     if (n_rhs < 1 || n_rhs > c->max_rhs) return fail(LS_ERR_ARG, "n_rhs outside [1, max_rhs]");
     if ((rc = check_disjoint(c, u, Au, n_rhs, sizeof(z128), "ls_apply"))) return rc;
+    if ((rc = order_begin(c, {reads(c, u, n_rhs), writes(c, Au, n_rhs)}))) return rc;
     return apply_op<double>(c, RhsSet::uniform(n_rhs, i_omega), (const z128*)u, (z128*)Au);
 }
 
@@ -707,6 +737,7 @@ int ls_apply_noalloc(ls_ctx* c, int i_omega, const void* u, void* Au, int n_rhs)
                                     std::to_string(kScratchBytes) + "-byte scratch (3 N3 L2 L1 x 16 bytes per right-hand side)");
     char* base = static_cast<char*>(scratch_address(c->device));
     if (!base) return fail(LS_ERR_STATE, "scratch address not set up on the context's device");
+    if ((rc = order_begin(c, {reads(c, u, n_rhs), writes(c, Au, n_rhs), {base, kScratchBytes, true}}))) return rc;
     return apply_op_in<double>(c, RhsSet::uniform(n_rhs, i_omega), (const z128*)u, (z128*)Au, (z128*)base,
                                tau ? (z128*)(base + work_al) : nullptr);
 }
@@ -718,6 +749,7 @@ int ls_apply_c64(ls_ctx* c, int i_omega, const void* u, void* Au, int n_rhs) {
     if (!u || !Au) return fail(LS_ERR_ARG, "null field pointer");
     if (n_rhs < 1 || n_rhs > c->max_rhs) return fail(LS_ERR_ARG, "n_rhs outside [1, max_rhs]");
     if ((rc = check_disjoint(c, u, Au, n_rhs, sizeof(z64), "ls_apply_c64"))) return rc;
+    if ((rc = order_begin(c, {reads(c, u, n_rhs, sizeof(z64)), writes(c, Au, n_rhs, sizeof(z64))}))) return rc;
     return apply_op<float>(c, RhsSet::uniform(n_rhs, i_omega), (const z64*)u, (z64*)Au);
 }
 
@@ -727,6 +759,7 @@ int ls_apply_T(ls_ctx* c, int i_omega, const void* y, void* ATy, int n_rhs) {
     if (!y || !ATy) return fail(LS_ERR_ARG, "null field pointer");
     if (n_rhs < 1 || n_rhs > c->max_rhs) return fail(LS_ERR_ARG, "n_rhs outside [1, max_rhs]");
     if ((rc = check_disjoint(c, y, ATy, n_rhs, sizeof(z128), "ls_apply_T"))) return rc;
+    if ((rc = order_begin(c, {reads(c, y, n_rhs), writes(c, ATy, n_rhs)}))) return rc;
     return apply_T_op<double>(c, RhsSet::uniform(n_rhs, i_omega), (const z128*)y, (z128*)ATy);
 }
 
@@ -735,6 +768,7 @@ int ls_convolve(ls_ctx* c, int i_omega, const void* f, void* out, int n_rhs) {
     if ((rc = check_ctx(c)) || (rc = check_omega(c, i_omega))) return rc;
     if (!f || !out) return fail(LS_ERR_ARG, "null field pointer");
     if (n_rhs < 1 || n_rhs > c->max_rhs) return fail(LS_ERR_ARG, "n_rhs outside [1, max_rhs]");
+    if ((rc = order_begin(c, {reads(c, f, n_rhs), writes(c, out, n_rhs)}))) return rc;
     return convolve_op<double>(c, RhsSet::uniform(n_rhs, i_omega), (const z128*)f, (z128*)out);
 }
 
@@ -750,6 +784,8 @@ int ls_solve_T(ls_ctx* c, int i_omega, const void* b, int n_rhs, double tol, int
     if (precision == LS_PREC_MIXED && !c->mixed)
         return fail(LS_ERR_STATE, "mixed precision needs a context built with LS_PREC_MIXED");
     if ((rc = check_solve_buffers(c, b, x0, x_out, n_rhs))) return rc;
+    const WaitingCall call(c, {reads(c, b, n_rhs), reads(c, x0, n_rhs), writes(c, x_out, n_rhs)});
+    if (call.rc) return call.rc;
     const std::vector<int> freq(n_rhs, i_omega);
     return solve_systems(c, freq.data(), (const z128*)b, n_rhs, tol, maxit, precision, (const z128*)x0, (z128*)x_out,
                          info, true);
@@ -760,6 +796,8 @@ int ls_grad_contrast(ls_ctx* c, int i_omega, const void* u, const void* mu, int 
     if ((rc = check_ctx(c)) || (rc = check_omega(c, i_omega))) return rc;
     if (!u || !mu || !g_dC || !g_drho) return fail(LS_ERR_ARG, "null pointer");
     if (n_rhs < 1) return fail(LS_ERR_ARG, "n_rhs must be >= 1");
+    const size_t cells = (size_t)c->ncell * sizeof(double);
+    if ((rc = order_begin(c, {reads(c, u, n_rhs), reads(c, mu, n_rhs), {g_dC, 21 * cells, true}, {g_drho, cells, true}}))) return rc;
     return grad_contrast_launch(c, i_omega, (const z128*)u, (const z128*)mu, false, n_rhs, g_dC, g_drho);
 }
 
@@ -776,6 +814,8 @@ int ls_grad(ls_ctx* c, int i_omega, const void* u, const void* lam_bar, int n_rh
             if (!std::isfinite(t0[r])) return fail(LS_ERR_ARG, "non-finite source time");
         }
     }
+    const size_t cells = (size_t)c->ncell * sizeof(double);
+    if ((rc = order_begin(c, {reads(c, u, n_rhs), reads(c, lam_bar, n_rhs), {g_dC, 21 * cells, true}, {g_drho, cells, true}}))) return rc;
     z128* muc = (z128*)c->gs;  // conj(mu) = Gconv lam_bar, in the workspace of the transposed operator
     if ((rc = convolve_op<double>(c, RhsSet::uniform(n_rhs, i_omega), (const z128*)lam_bar, muc))) return rc;
     if ((rc = grad_contrast_launch(c, i_omega, (const z128*)u, muc, true, n_rhs, g_dC, g_drho))) return rc;
@@ -788,15 +828,17 @@ int ls_rhs_moment(ls_ctx* c, int i_omega, const double M[6], const int src[3], d
     int rc;
     if ((rc = check_moment(c, i_omega, M, src, t0))) return rc;
     if (!b) return fail(LS_ERR_ARG, "null argument");
+    const WaitingCall call(c, {writes(c, b, 1)});
+    if (call.rc) return call.rc;
     return rhs_moment_into(c, i_omega, M, src, t0, (z128*)b);
 }
 
 int ls_rhs_force(ls_ctx* c, int i_omega, const double F[3], const int cell[3], void* b) {
     int rc;
-    if ((rc = check_ctx(c)) || (rc = check_omega(c, i_omega)) || (rc = check_cell(c, cell))) return rc;
-    if (!F || !b) return fail(LS_ERR_ARG, "null argument");
-    for (int a = 0; a < 3; ++a)
-        if (!std::isfinite(F[a])) return fail(LS_ERR_ARG, "non-finite force");
+    if ((rc = check_force(c, i_omega, F, cell))) return rc;
+    if (!b) return fail(LS_ERR_ARG, "null argument");
+    const WaitingCall call(c, {writes(c, b, 1)});
+    if (call.rc) return call.rc;
     return rhs_points_launch(c, i_omega, cell, F, 1, 0.0, (z128*)b);
 }
 
@@ -812,6 +854,8 @@ int ls_solve(ls_ctx* c, int i_omega, const void* b, int n_rhs, double tol, int m
     if (precision == LS_PREC_MIXED && !c->mixed)
         return fail(LS_ERR_STATE, "mixed precision needs a context built with LS_PREC_MIXED");
     if ((rc = check_solve_buffers(c, b, x0, u_out, n_rhs))) return rc;
+    const WaitingCall call(c, {reads(c, b, n_rhs), reads(c, x0, n_rhs), writes(c, u_out, n_rhs)});
+    if (call.rc) return call.rc;
     const std::vector<int> freq(n_rhs, i_omega);
     return solve_systems(c, freq.data(), (const z128*)b, n_rhs, tol, maxit, precision, (const z128*)x0, (z128*)u_out,
                          info);
@@ -831,21 +875,23 @@ int ls_solve_multi(ls_ctx* c, const int* i_omega, const void* b, int n_rhs, doub
     if (precision == LS_PREC_MIXED && !c->mixed)
         return fail(LS_ERR_STATE, "mixed precision needs a context built with LS_PREC_MIXED");
     if ((rc = check_solve_buffers(c, b, x0, u_out, n_rhs))) return rc;
+    const WaitingCall call(c, {reads(c, b, n_rhs), reads(c, x0, n_rhs), writes(c, u_out, n_rhs)});
+    if (call.rc) return call.rc;
     return solve_systems(c, i_omega, (const z128*)b, n_rhs, tol, maxit, precision, (const z128*)x0, (z128*)u_out,
                          info);
 }
 
 int ls_solve_moment(ls_ctx* c, int i_omega, const double M[6], const int src[3], double t0, double tol, int maxit,
                     int precision, const void* x0, void* u_out, ls_info* info) {
-    int rc = ls_rhs_moment(c, i_omega, M, src, t0, c ? (void*)c->bd : nullptr);
-    if (rc) return rc;
+    int rc;
+    if ((rc = check_moment(c, i_omega, M, src, t0)) || (rc = rhs_moment_into(c, i_omega, M, src, t0, c->bd))) return rc;
     return ls_solve(c, i_omega, c->bd, 1, tol, maxit, precision, x0, u_out, info);
 }
 
 int ls_solve_force(ls_ctx* c, int i_omega, const double F[3], const int cell[3], double tol, int maxit, int precision,
                    void* u_out, ls_info* info) {
-    int rc = ls_rhs_force(c, i_omega, F, cell, c ? (void*)c->bd : nullptr);
-    if (rc) return rc;
+    int rc;
+    if ((rc = check_force(c, i_omega, F, cell)) || (rc = rhs_points_launch(c, i_omega, cell, F, 1, 0.0, c->bd))) return rc;
     return ls_solve(c, i_omega, c->bd, 1, tol, maxit, precision, nullptr, u_out, info);
 }
 
@@ -929,6 +975,15 @@ int ls_solve_batch(ls_ctx* const* ctxs, int n_ctx, const ls_job* jobs, int n_job
         for (size_t k = 0; k < mine.size(); k += (size_t)ctxs[i]->max_rhs)
             plan[i].emplace_back(mine.begin() + k, mine.begin() + std::min(mine.size(), k + (size_t)ctxs[i]->max_rhs));
     }
+    std::vector<std::unique_ptr<WaitingCall>> calls;
+    for (int i = 0; i < n_ctx; ++i) {
+        std::vector<Span> spans;
+        for (const auto& batch : plan[i])
+            for (int j : batch) spans.push_back(writes(ctxs[i], jobs[j].u_out, 1));
+        if (spans.empty()) continue;
+        calls.emplace_back(new WaitingCall(ctxs[i], spans.data(), (int)spans.size()));
+        if (calls.back()->rc) return calls.back()->rc;
+    }
     // one worker per context with work, each driving its context's stream (the solves synchronise
     // for their convergence tests, so contexts on different streams overlap on the device)
     std::vector<int> codes(n_ctx, LS_OK);
@@ -975,6 +1030,8 @@ int ls_sample(ls_ctx* c, const void* u, int n_rhs, const int* rec, int n_rec, vo
     if (n_rhs < 1 || n_rec < 1) return fail(LS_ERR_ARG, "n_rhs and n_rec must be >= 1");
     for (int m = 0; m < n_rec; ++m)
         if ((rc = check_cell(c, rec + 3 * m))) return rc;
+    const WaitingCall call(c, {reads(c, u, n_rhs), {out, (size_t)n_rhs * n_rec * 3 * sizeof(z128), true}});
+    if (call.rc) return call.rc;
     return sample_launch(c, (const z128*)u, n_rhs, rec, n_rec, (z128*)out);
 }
 
@@ -988,6 +1045,9 @@ int ls_synthesize(ls_ctx* c, const void* spectra, const int* k, int n_freq, int 
         return fail(LS_ERR_ARG, "dt must be positive; dt, fp, ts finite");
     for (int q = 0; q < n_freq; ++q)
         if (k[q] < 0 || 2 * k[q] > nt) return fail(LS_ERR_ARG, "frequency index outside [0, nt/2]");
+    const WaitingCall call(c, {{spectra, (size_t)n_freq * n_trace * sizeof(z128), false},
+                               {traces, (size_t)n_trace * nt * sizeof(double), true}});
+    if (call.rc) return call.rc;
     return synthesize_launch(c, (const z128*)spectra, k, n_freq, n_trace, nt, dt, fp, ts, traces);
 }
 
@@ -998,6 +1058,7 @@ int ls_strain(ls_ctx* c, const void* u, void* eps, int n_rhs) {
     if (n_rhs < 1) return fail(LS_ERR_ARG, "n_rhs must be >= 1");
     if (overlaps(u, (size_t)n_rhs * c->field_elems() * sizeof(z128), eps, 2 * (size_t)n_rhs * c->field_elems() * sizeof(z128)))
         return fail(LS_ERR_ARG, "ls_strain: u and eps overlap");
+    if ((rc = order_begin(c, {reads(c, u, n_rhs), {eps, 2 * (size_t)n_rhs * c->field_elems() * sizeof(z128), true}}))) return rc;
     return strain_launch(c, (const z128*)u, (z128*)eps, n_rhs);
 }
 

@@ -163,6 +163,30 @@ struct Profiler {
 };
 
 // ------------------------------------------------------------------------------------------
+// order between private streams; see order.hip
+
+// a range of caller memory that a call reads or writes
+struct Span {
+    const void* p;
+    size_t bytes;
+    bool write;
+};
+
+// the ranges of a context's calls that may still be running; the first `covered` of them belong to calls before the
+// event's last record
+struct StreamOrder {
+    struct Range {
+        uintptr_t lo, hi;
+        bool write;
+    };
+    static constexpr int kMax = 32;
+    Range range[kMax];
+    int n = 0, covered = 0;
+    bool waiting = false;   // inside a call that waits for its stream before it returns
+    hipEvent_t ev = nullptr;
+};
+
+// ------------------------------------------------------------------------------------------
 // context
 
 struct Ctx {
@@ -181,8 +205,9 @@ struct Ctx {
     double C0[36] = {0};          // background stiffness as given
     std::vector<double> omega;
     hipStream_t stream = nullptr;
-    hipStream_t own_stream = nullptr;  // created when the caller passes the null stream (a blocking stream,
-                                       // so it stays ordered with work on the legacy default stream)
+    hipStream_t own_stream = nullptr;  // when the caller passes the null stream: a blocking stream, so it stays ordered
+                                       // with work on the legacy default stream
+    StreamOrder order;                 // its order with the private streams of other contexts
     int flags = 0;
     int num_cu = 256;  // compute units of the device (block-count heuristics)
     int device = 0;    // the HIP device the context was set up on
@@ -272,6 +297,31 @@ struct Ctx {
     const z128* twiddle128(int L) const;
     const z64* twiddle64(int L) const;
     size_t field_elems() const { return (size_t)3 * (size_t)ncell; }
+};
+
+// a private stream for the context
+int private_stream(Ctx* c);
+void private_stream_release(Ctx* c);
+// Before a call that returns without waiting: wait on the device for conflicting calls of other contexts, and note the
+// ranges.  Around a call that waits for its stream: nothing stays noted.  No-ops on a caller's stream.
+int order_begin(Ctx* c, const Span* s, int ns);
+int order_begin_waiting(Ctx* c, const Span* s, int ns);
+void order_end_waiting(Ctx* c);
+template <int N>
+int order_begin(Ctx* c, const Span (&s)[N]) {
+    return order_begin(c, s, N);
+}
+struct WaitingCall {
+    Ctx* c;
+    int rc;
+    WaitingCall(Ctx* ctx, const Span* s, int ns) : c(ctx), rc(order_begin_waiting(ctx, s, ns)) {}
+    template <int N>
+    WaitingCall(Ctx* ctx, const Span (&s)[N]) : WaitingCall(ctx, s, N) {}
+    ~WaitingCall() {
+        if (rc == LS_OK) order_end_waiting(c);
+    }
+    WaitingCall(const WaitingCall&) = delete;
+    WaitingCall& operator=(const WaitingCall&) = delete;
 };
 
 // device allocation tracked in ctx->bytes

@@ -447,9 +447,9 @@ class Context:
                                (0 if graphs else LS_FLAG_NO_GRAPH) | (LS_FLAG_AUTOTUNE if autotune else 0),
                                int(taper), int(bicgstab_l), PRECONDS[precond])
         del dc, dr
-        # On the default stream the library works on a private one.  Outputs are allocated on that stream, so that the
-        # allocator hands a dropped output's memory only to later work of this context: work of another context
-        # is not ordered with what may still be writing it.
+        # On the default stream the library works on a private one.  Outputs are allocated on that stream, so that a
+        # dropped output's memory goes to later work of this context and contexts do not wait for one another (the
+        # library orders calls of different contexts that touch the same memory).
         own = ls_stream(self.handle)
         self._pool = torch.cuda.ExternalStream(own, device=self.device) if self.stream.cuda_stream == 0 else None
         self._index = self._device_index().index
