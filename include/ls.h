@@ -371,7 +371,8 @@ int ls_contrast_format(const ls_ctx* ctx);
 /* The hipStream_t the context's work runs on: the one it was set up with or, set up on the null stream, a private
  * blocking stream.  That one is ordered with the null stream, and with the private stream of another context as far as
  * their calls touch the same memory: a call waits on the device for earlier calls of other such contexts that write what
- * it reads or writes, or read what it writes.  NULL for a null context. */
+ * it reads or writes, or read what it writes.  The stream outlives the context and goes to a later one.  NULL for a
+ * null context. */
 void* ls_stream(const ls_ctx* ctx);
 
 /* Message of the last error on this host thread ("" if none). */

@@ -299,7 +299,9 @@ struct Ctx {
     size_t field_elems() const { return (size_t)3 * (size_t)ncell; }
 };
 
-// a private stream for the context
+// A private stream for the context, from those of destroyed contexts where there is one: a stream-ordered allocator of the
+// caller keeps memory per stream, which a new context then finds again.  Not more streams exist than contexts did at
+// one time.
 int private_stream(Ctx* c);
 void private_stream_release(Ctx* c);
 // Before a call that returns without waiting: wait on the device for conflicting calls of other contexts, and note the

@@ -1,4 +1,4 @@
-// Order between the private streams of contexts set up on the null stream.
+// Order between the private streams of contexts set up on the null stream, and the streams themselves.
 //
 // The runtime orders such a stream with the caller's work on the null stream, but not with the private stream of another
 // context, and most calls return before their work is done.  So every call states the ranges of caller memory it reads
@@ -15,8 +15,10 @@ namespace ls {
 
 namespace {
 
+constexpr int kMaxStreamDevices = 64;
 std::mutex g_order_mutex;            // guards everything below and Ctx::order of every context
 std::vector<Ctx*> g_private;         // live contexts on private streams
+std::vector<hipStream_t> g_idle_streams[kMaxStreamDevices];
 
 bool conflict(const StreamOrder::Range* a, int na, const Span* s, int ns) {
     for (int i = 0; i < na; ++i)
@@ -125,12 +127,16 @@ void order_end_waiting(Ctx* c) {
 
 int private_stream(Ctx* c) {
     std::lock_guard<std::mutex> lock(g_order_mutex);
-    if (hipStreamCreate(&c->own_stream) != hipSuccess) {
+    auto& idle = g_idle_streams[c->device % kMaxStreamDevices];
+    hipStream_t s = nullptr;
+    if (!idle.empty()) {
+        s = idle.back();
+        idle.pop_back();
+    } else if (hipStreamCreate(&s) != hipSuccess) {
         (void)hipGetLastError();
-        c->own_stream = nullptr;
         return fail(LS_ERR_HIP, "stream creation failed");
     }
-    c->stream = c->own_stream;
+    c->own_stream = c->stream = s;
     if (hipEventCreateWithFlags(&c->order.ev, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
         c->order.ev = nullptr;
@@ -145,7 +151,7 @@ void private_stream_release(Ctx* c) {
     std::lock_guard<std::mutex> lock(g_order_mutex);
     g_private.erase(std::remove(g_private.begin(), g_private.end(), c), g_private.end());
     if (c->order.ev) (void)hipEventDestroy(c->order.ev);
-    (void)hipStreamDestroy(c->own_stream);
+    g_idle_streams[c->device % kMaxStreamDevices].push_back(c->own_stream);
     c->own_stream = c->stream = nullptr;
 }
 

@@ -440,13 +440,20 @@ class Context:
         dc = torch.as_tensor(np.asarray(dc21, dtype=np.float64)).reshape(21, n3, n2, n1).to(self.device).contiguous()
         dr = torch.as_tensor(np.asarray(drho, dtype=np.float64)).reshape(n3, n2, n1).to(self.device).contiguous()
         self.stream = torch.cuda.current_stream(self.device)
-        self.handle = ls_setup(self.shape, h, C0, rho0, dc, dr, self.omegas,
-                               LS_PREC_MIXED if self.mixed else LS_PREC_C128,
-                               GREEN_MODES[green_mode], max_rhs,
-                               self.stream.cuda_stream,
-                               (0 if graphs else LS_FLAG_NO_GRAPH) | (LS_FLAG_AUTOTUNE if autotune else 0),
-                               int(taper), int(bicgstab_l), PRECONDS[precond])
-        del dc, dr
+        args = (self.shape, h, C0, rho0, dc, dr, self.omegas,
+                LS_PREC_MIXED if self.mixed else LS_PREC_C128,
+                GREEN_MODES[green_mode], max_rhs,
+                self.stream.cuda_stream,
+                (0 if graphs else LS_FLAG_NO_GRAPH) | (LS_FLAG_AUTOTUNE if autotune else 0),
+                int(taper), int(bicgstab_l), PRECONDS[precond])
+        try:
+            self.handle = ls_setup(*args)
+        except LsError as e:
+            if e.code != LS_ERR_OOM:
+                raise
+            torch.cuda.empty_cache()   # the library allocates past torch's cache, which may hold what it needs
+            self.handle = ls_setup(*args)
+        del dc, dr, args
         # On the default stream the library works on a private one.  Outputs are allocated on that stream, so that a
         # dropped output's memory goes to later work of this context and contexts do not wait for one another (the
         # library orders calls of different contexts that touch the same memory).
