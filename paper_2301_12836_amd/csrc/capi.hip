@@ -635,14 +635,15 @@ int ls_setup(const ls_grid* grid, const double C0[36], double rho0, const double
             rc = fail(LS_ERR_OOM, "pinned host allocation failed");
         }
     }
-    // twiddle tables e^{-2 pi i m / L} computed in FP64 on the host
+    // twiddle tables e^{-2 pi i m / L}, rounded from extended precision (in FP64 the angle's own rounding alone is of the
+    // size of the result's)
     for (int L : {c->L1, c->L2, c->L3}) {
         if (rc || c->twiddle128(L)) continue;
         std::vector<z128> h128(L);
         std::vector<z64> h64(L);
         for (int m = 0; m < L; ++m) {
-            const double ang = -2.0 * 3.14159265358979323846 * (double)m / (double)L;
-            h128[m] = {std::cos(ang), std::sin(ang)};
+            const long double ang = -2.0L * 3.14159265358979323846264338327950288L * m / L;
+            h128[m] = {(double)std::cos(ang), (double)std::sin(ang)};
             h64[m] = {(float)h128[m].x, (float)h128[m].y};
         }
         z128* d128 = nullptr;

@@ -205,23 +205,31 @@ __device__ __forceinline__ void reg_dft3(cpx<T>* v) {
     }
 }
 
-// cos and sin of 2 pi m / N
+// cos and sin of 2 pi m / N, to 32 digits: the compiler rounds them to the nearest value of the precision
 template <int N>
 struct Roots;
 template <>
 struct Roots<9> {
-    static constexpr double c[5] = {1.0, 0.766044443118978, 0.17364817766693041, -0.4999999999999998, -0.9396926207859083};
-    static constexpr double s[5] = {0.0, 0.6427876096865393, 0.984807753012208, 0.8660254037844387, 0.3420201433256689};
+    static constexpr double c[5] = {1.0, 0.76604444311897803520239265055542, 0.17364817766693034885171662676931, -0.5,
+                                    -0.93969262078590838405410927732473};
+    static constexpr double s[5] = {0.0, 0.64278760968653932632264340990726, 0.98480775301220805936674302458952,
+                                    0.86602540378443864676372317075294, 0.34202014332566873304409961468226};
 };
 template <>
 struct Roots<10> {
-    static constexpr double c[5] = {1.0, 0.8090169943749475, 0.30901699437494745, -0.30901699437494734, -0.8090169943749473};
-    static constexpr double s[5] = {0.0, 0.5877852522924731, 0.9510565162951535, 0.9510565162951536, 0.5877852522924732};
+    static constexpr double c[5] = {1.0, 0.80901699437494742410229341718282, 0.30901699437494742410229341718282,
+                                    -0.30901699437494742410229341718282, -0.80901699437494742410229341718282};
+    static constexpr double s[5] = {0.0, 0.58778525229247312916870595463907, 0.95105651629515357211643933337938,
+                                    0.95105651629515357211643933337938, 0.58778525229247312916870595463907};
 };
 template <>
 struct Roots<14> {
-    static constexpr double c[7] = {1.0, 0.9009688679024191, 0.6234898018587336, 0.22252093395631445, -0.22252093395631434, -0.6234898018587335, -0.900968867902419};
-    static constexpr double s[7] = {0.0, 0.4338837391175581, 0.7818314824680298, 0.9749279121818236, 0.9749279121818236, 0.7818314824680299, 0.43388373911755823};
+    static constexpr double c[7] = {1.0, 0.90096886790241912623610231950745, 0.62348980185873353052500488400424,
+                                    0.22252093395631440428890256449679, -0.22252093395631440428890256449679,
+                                    -0.62348980185873353052500488400424, -0.90096886790241912623610231950745};
+    static constexpr double s[7] = {0.0, 0.43388373911755812047576833284836, 0.78183148246802980870844452667406,
+                                    0.97492791218182360701813168299393, 0.97492791218182360701813168299393,
+                                    0.78183148246802980870844452667406, 0.43388373911755812047576833284836};
 };
 
 // In-register DFT of length N = P Q (9, 10, 14) with sign SIGN, natural order in and out: with n = a + P b and
