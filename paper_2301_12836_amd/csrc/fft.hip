@@ -187,7 +187,9 @@ __global__ __launch_bounds__(TX * FourStep<L>::N1) void k_fs_strided(cpx<T>* __r
 // Strided pass at the lengths L = A x 16, A no power of two (3, 5, 6, 7, 9, 10, 12, 14): the asymmetric four-step of the
 // z pass (fft_z.hip) over 16 threads per column.  Forward: natural input (threads
 // q < A hold elements q + A j), outputs X[q + 16 k1] in slot k1; inverse: the reverse, natural outputs.
-// Threads q >= A transform zeros or a copy of row A - 1 and write nothing (no divergent merge).
+// Threads q >= A transform zeros or a copy of row A - 1 and write nothing (no divergent merge).  The inverse takes whole
+// lines (n_in = L), so its loads need no branches, in which the compiler would also convert the values of the FP64 DFTs
+// (reg_dft_pq), each behind a wait for its own load (y inverse at 112^3, 3 FP32 right-hand sides: 0.172 against 0.098 ms).
 template <typename T, int L, int TX, int SIGN, bool PRUNE>
 __global__ __launch_bounds__(TX * 16) void k_fs_strided3(cpx<T>* __restrict__ data, long long S1, long long S2,
                                                           long long ES, int n_in, int n_out,
@@ -227,10 +229,7 @@ __global__ __launch_bounds__(TX * 16) void k_fs_strided3(cpx<T>* __restrict__ da
         }
     } else {
 #pragma unroll
-        for (int k1 = 0; k1 < A; ++k1) {
-            const int k = q + B * k1;
-            v[k1] = k < n_in ? load_nt(&base[k * ES]) : cpx<T>{T(0), T(0)};
-        }
+        for (int k1 = 0; k1 < A; ++k1) v[k1] = load_nt(&base[(q + B * k1) * ES]);
         __syncthreads();
         reg_dft_any<SIGN, A, T>(v);
 #pragma unroll
@@ -497,7 +496,10 @@ __global__ __launch_bounds__(TY * 16) void k_fs_contig3(cpx<T>* __restrict__ dat
     const long long line = (long long)blockIdx.x * TY + ln;
     const bool valid = line < nlines;
     const long long orow = (MODE == 0 || !valid) ? 0 : slot_row(line, lpr, line_position<TY>(line, lpr), sm, D2, zbs);
-    const long long o1 = line / D2, o2 = line - o1 * D2;
+    // FP64 DFTs of FP32 values take their input without branches, as in k_fs_strided3: lines past the last one read that one.
+    // The others keep the branch (96^3, 6 FP32 right-hand sides: 0.092 against 0.096 ms).
+    constexpr bool kWideDft = SIGN > 0 && sizeof(T) == 4 && (A % 7 == 0 || A == 9);
+    const long long in_line = !kWideDft || valid ? line : nlines - 1, o1 = in_line / D2, o2 = in_line - o1 * D2;
     cpx<T>* base = data + o1 * S1 + o2 * S2;
     const bool s1 = q < A;
     const int qa = s1 ? q : A - 1;
@@ -532,7 +534,7 @@ __global__ __launch_bounds__(TY * 16) void k_fs_contig3(cpx<T>* __restrict__ dat
 #pragma unroll
         for (int k1 = 0; k1 < A; ++k1) {
             const int k = q + B * k1;
-            v[k1] = (valid && k < n_in) ? load_nt(&base[k]) : cpx<T>{T(0), T(0)};
+            v[k1] = (kWideDft || (valid && k < n_in)) ? load_nt(&base[k]) : cpx<T>{T(0), T(0)};
         }
         // the epilogue's u (and r^ for DOT 1) requested before the transform
         cpx<T> up[B], ap[B];

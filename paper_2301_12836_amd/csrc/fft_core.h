@@ -151,9 +151,19 @@ template <int SIGN, typename T>
 struct SmallDft<SIGN, 5, T> {
     static __device__ __forceinline__ void run(cpx<T>* v) { odd_dft<SIGN, 5, T>(v); }
 };
+// In FP32 the sums of the length-7 DFT are formed in FP64 and rounded once: in FP32 they round more often than the length-8
+// DFT that the next power of two has in its place.  Relative L2 error of an FP32 application at 56^3 (length 112): 8.4e-8
+// with FP32 sums, 7.1e-8 with these, 7.5e-8 at length 128.
 template <int SIGN, typename T>
 struct SmallDft<SIGN, 7, T> {
-    static __device__ __forceinline__ void run(cpx<T>* v) { odd_dft<SIGN, 7, T>(v); }
+    static __device__ __forceinline__ void run(cpx<T>* v) {
+        cpx<double> w[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) w[j] = {(double)v[j].x, (double)v[j].y};
+        odd_dft<SIGN, 7, double>(w);
+#pragma unroll
+        for (int j = 0; j < 7; ++j) v[j] = {(T)w[j].x, (T)w[j].y};
+    }
 };
 
 // the odd factors first (at NS = 1 the first needs no twiddles), then 8, 4, 2

@@ -233,29 +233,38 @@ struct Roots<14> {
 };
 
 // In-register DFT of length N = P Q (9, 10, 14) with sign SIGN, natural order in and out: with n = a + P b and
-// k = k2 + Q k1, length-Q DFTs of each residue a, the twiddles W_N^{a k2}, then length-P DFTs.
+// k = k2 + Q k1, length-Q DFTs of each residue a, the twiddles W_N^{a k2}, then length-P DFTs.  FP32 at 9 and 14: the odd
+// DFTs and the twiddles in FP64, with one rounding between the stages, for the reason of SmallDft<., 7, .>.  Relative L2
+// error of an FP32 application with FP32 sums, with these, and at the next length 2^a or 3 2^a: 72^3 (144) 10.5e-8, 7.7e-8,
+// 8.9e-8; 112^3 (224) 11.9e-8, 9.4e-8, 10.9e-8.  What they cost: the z pass 0.070 -> 0.078 ms at 72^3 with 3 right-hand
+// sides, 0.245 -> 0.294 at 112^3; with FP64 values between the stages too it spills.  Length 10 in FP32 is below the
+// lengths it replaces as it is (80^3: 8.5e-8 against 9.5e-8).
 template <int SIGN, int P, int Q, typename T>
 __device__ __forceinline__ void reg_dft_pq(cpx<T>* v) {
     constexpr int N = P * Q;
+    using W = std::conditional_t<N == 10, T, double>;
     cpx<T> tmp[N];
 #pragma unroll
     for (int a = 0; a < P; ++a) {
-        cpx<T> w[Q];
+        cpx<W> w[Q];
 #pragma unroll
-        for (int b = 0; b < Q; ++b) w[b] = v[a + P * b];
-        SmallDft<SIGN, Q, T>::run(w);
+        for (int b = 0; b < Q; ++b) w[b] = {(W)v[a + P * b].x, (W)v[a + P * b].y};
+        SmallDft<SIGN, Q, W>::run(w);
 #pragma unroll
-        for (int k2 = 0; k2 < Q; ++k2)
-            tmp[a * Q + k2] = (a * k2 == 0) ? w[k2] : w[k2] * cpx<T>{T(Roots<N>::c[a * k2]), T(SIGN * Roots<N>::s[a * k2])};
+        for (int k2 = 0; k2 < Q; ++k2) {
+            if (a * k2 > 0) w[k2] = w[k2] * cpx<W>{W(Roots<N>::c[a * k2]), W(SIGN * Roots<N>::s[a * k2])};
+            tmp[a * Q + k2] = {(T)w[k2].x, (T)w[k2].y};
+        }
     }
+    using V = std::conditional_t<P == 2, T, W>;
 #pragma unroll
     for (int k2 = 0; k2 < Q; ++k2) {
-        cpx<T> w[P];
+        cpx<V> w[P];
 #pragma unroll
-        for (int a = 0; a < P; ++a) w[a] = tmp[a * Q + k2];
-        SmallDft<SIGN, P, T>::run(w);
+        for (int a = 0; a < P; ++a) w[a] = {(V)tmp[a * Q + k2].x, (V)tmp[a * Q + k2].y};
+        SmallDft<SIGN, P, V>::run(w);
 #pragma unroll
-        for (int k1 = 0; k1 < P; ++k1) v[k2 + Q * k1] = w[k1];
+        for (int k1 = 0; k1 < P; ++k1) v[k2 + Q * k1] = {(T)w[k1].x, (T)w[k1].y};
     }
 }
 
