@@ -175,12 +175,13 @@ struct ZLine {
 
 // Waves per SIMD of the register z pass.  FP64 at 384 needs 75 registers more than two waves leave: 3.02 ms (2
 // right-hand sides at 192^3) against 2.54 ms with one wave; 224 (3 at 112^3: 0.61 against 0.54 ms) and 448 60 and 170;
-// the half-space table's index work at 512 as many.  At 320 the two waves pay (160^3 0.72 against 0.81 ms).  FP32
-// with four waves spills as well (0.86 against 0.74 ms at 128^3).
+// the half-space table's index work at 512 as many.  At 320 the two waves pay (160^3 0.72 against 0.81 ms).  FP32: three
+// up to 256 (four spill as well, 0.86 against 0.74 ms at 128^3; two are slower at 224, 3 right-hand sides at 112^3 0.310
+// against 0.294 ms); above, blocks of 512 threads are two waves a SIMD, and a second block would need four (a cap of three
+// spills 29-57 registers at 448: one right-hand side at 224^3 1.37 against 1.17 ms; 288 to 384 and 512 take the same time).
 template <typename T, int L, bool HALF>
 constexpr int z_waves() {
-    constexpr bool big = L == 512 && HALF;
-    return sizeof(T) == 8 ? (L == 224 || L == 384 || L == 448 || big ? 1 : 2) : (big ? 2 : 3);
+    return sizeof(T) == 8 ? (L == 224 || L == 384 || L == 448 || (L == 512 && HALF) ? 1 : 2) : (L > 256 ? 2 : 3);
 }
 
 // Scheduling fence between the components of the register z pass: above 256 it saves the registers of the second wave
