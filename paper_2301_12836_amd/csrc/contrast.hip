@@ -667,10 +667,7 @@ inline int fused_z_chunk(int n3, long long cols, long long slots) {
 
 // Tile, block size and resident blocks per CU.  FP64: 32 x 8 cells, 384 threads (256 owned, 80 halo), 145 KB LDS, one
 // block.  FP32: 32 x 4 cells, 256 threads (128 owned, 72 halo), 47 KB LDS, three blocks; or the narrow tile, 16 x 8
-// cells, 192 threads (48 halo), 40 KB, four blocks.  The narrow one does less halo work and wastes less of grids that are
-// no multiple of 32 wide, but reads half lines; it is the faster where the grid's fields stay in the caches (96^3, 3
-// right-hand sides, 21 entries: 85 against 93 us; 48^3, 6: 27 against 34) and the slower from 128^3 on (142.7 against
-// 148 us with 2 right-hand sides; 256^3 629 against 860).
+// cells, 192 threads (48 halo), 40 KB, four blocks.  The narrow one does less halo work, but reads half lines.
 template <typename T, bool NARROW>
 struct FusedShape;
 template <>
@@ -689,12 +686,20 @@ struct FusedShape<double, false> {
     static constexpr bool DB = false;
 };
 
-// whether the FP32 kernel takes the narrow tile: grids up to a million cells, or a fifth fewer cells in its tiles
+// Whether the FP32 kernel takes the narrow tile: where it covers a fifth fewer cells than the wide one, and on grids up to a
+// million cells where it covers a sixth fewer.  Wide / narrow in us with 1, 2, 3, 4, 6 right-hand sides, 21 entries:
+//   3/4 of the cells: 48^3 15.5/14.0 18.3/16.8 22.7/19.6 25.2/21.7 33.9/26.8; 48x200x160 76/69 133/116 178/162 249/198 343/291
+//   5/6: 72x55x41 18.5/16.2 23.2/20.6 27.8/25.5 35.9/35.4 44.7/41.3; 72^3 26.0/23.6 37.6/39.1 52.4/47.6 65.1/59.9 91.8/76.5;
+//        80^3 28.8/28.1 45.1/46.9 57.9/58.4 74.3/78.2 106/95.8; but 72x200x200 135/147 241/255 350/299 455/501
+//   7/8: 104^3 51/60 97/95 143/125 186/156 272/223
+//   all: 64^3 18.6/18.2 25.5/23.4 30.5/33.6 38.1/47.0 50.7/55.8; 96^3 36.8/44.8 60.6/71.5 90/83 120/123 179/172
+// (where neither is the better one for every number of right-hand sides the wide one stays: the packed contrast has one layout).
 template <typename T>
 bool narrow_tile(const Ctx* c) {
     if (sizeof(T) == 8) return false;
     auto covered = [&](int bx, int by) { return (long long)((c->n1 + bx - 1) / bx * bx) * ((c->n2 + by - 1) / by * by); };
-    return c->ncell <= 1000000 || covered(16, 8) * 5 < covered(32, 4) * 4;
+    const long long n = covered(16, 8), w = covered(32, 4);
+    return n * 5 < w * 4 || (c->ncell <= 1000000 && n * 6 <= w * 5);
 }
 
 template <typename T, bool NARROW>
