@@ -757,7 +757,7 @@ int bicgstab(Ctx* c, const RhsSet& all, const cpx<T>* b, cpx<X>* x, const cpx<T>
 //                  u_{j+1} = A u_j;  alpha = rho0 / (r^H u_{j+1});  r_i -= alpha u_{i+1} (i <= j);
 //                  x += alpha u_0;  r_{j+1} = A r_j
 //   MR part:       gamma = argmin ||r_0 - sum_{j>=1} gamma_j r_j||, from the Gram matrix Z = R^H R
-//                  (normal equations, Cholesky on the host);  r_0 -= sum gamma_j r_j;
+//                  (normal equations, Cholesky on the host; see mr_coefficients);  r_0 -= sum gamma_j r_j;
 //                  u_0 -= sum gamma_j u_j;  x += sum gamma_j r_{j-1};  omega = gamma_l;  next rho0 = -omega rho0.
 // The scalars of the cycle are computed on the host from deterministic device reductions (fixed
 // block count and order), one round trip per inner product, so the iteration is not captured in a
@@ -928,9 +928,12 @@ struct LState {
     std::complex<double> rho0 = 1.0, alpha = 0.0, omega = 1.0;
 };
 
-// Solve min ||r_0 - sum_{j=1..l} g_j r_j|| from Z (upper triangle, row-major pairs): Z[1:,1:] g = Z[1:,0].
-bool mr_coefficients(const double* z, int l, std::complex<double>* g) {
+// Solve min ||r_0 - sum_{j=1..d} g_j r_j|| from Z (upper triangle, row-major pairs): Z[1:,1:] g = Z[1:,0], for the largest
+// degree d <= l whose normal equations factor.  Returns d (g_j = 0 above it), 0 if there is none.
+int mr_coefficients(const double* z, int l, std::complex<double>* g) {
     using C = std::complex<double>;
+    for (int q = 0; q < (l + 1) * (l + 2); ++q)
+        if (!std::isfinite(z[q])) return 0;
     // entry (a, b) of the Hermitian Gram matrix from its stored upper triangle
     auto Z = [&](int a, int b) -> C {
         const bool lower = a > b;
@@ -946,14 +949,18 @@ bool mr_coefficients(const double* z, int l, std::complex<double>* g) {
         for (int b = 0; b < l; ++b) M[a][b] = Z(a + 1, b + 1);
         rhs[a] = Z(a + 1, 0);
     }
-    // Cholesky M = L L^H
+    // Cholesky M = L L^H, as far as the pivots are positive (r_1 .. r_d, r_{d+1} linearly dependent to rounding beyond)
     C Lm[kMaxL][kMaxL] = {};
-    for (int a = 0; a < l; ++a) {
+    int d = l;
+    for (int a = 0; a < d; ++a) {
         for (int b = 0; b <= a; ++b) {
             C sacc = M[a][b];
             for (int k = 0; k < b; ++k) sacc -= Lm[a][k] * std::conj(Lm[b][k]);
             if (a == b) {
-                if (!(sacc.real() > 0.0) || !std::isfinite(sacc.real())) return false;
+                if (!(sacc.real() > 0.0) || !std::isfinite(sacc.real())) {
+                    d = a;
+                    break;
+                }
                 Lm[a][a] = std::sqrt(sacc.real());
             } else {
                 Lm[a][b] = sacc / Lm[b][b].real();
@@ -961,18 +968,19 @@ bool mr_coefficients(const double* z, int l, std::complex<double>* g) {
         }
     }
     C y[kMaxL];
-    for (int a = 0; a < l; ++a) {
+    for (int a = 0; a < d; ++a) {
         C sacc = rhs[a];
         for (int k = 0; k < a; ++k) sacc -= Lm[a][k] * y[k];
         y[a] = sacc / Lm[a][a].real();
     }
-    for (int a = l - 1; a >= 0; --a) {
+    for (int j = d + 1; j <= l; ++j) g[j] = 0.0;
+    for (int a = d - 1; a >= 0; --a) {
         C sacc = y[a];
-        for (int k = a + 1; k < l; ++k) sacc -= std::conj(Lm[k][a]) * g[k + 1];
+        for (int k = a + 1; k < d; ++k) sacc -= std::conj(Lm[k][a]) * g[k + 1];
         g[a + 1] = sacc / Lm[a][a].real();
-        if (!std::isfinite(g[a + 1].real()) || !std::isfinite(g[a + 1].imag())) return false;
+        if (!std::isfinite(g[a + 1].real()) || !std::isfinite(g[a + 1].imag())) return 0;
     }
-    return true;
+    return d;
 }
 
 template <typename T, typename X, typename ApplyFn>
@@ -991,7 +999,7 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
     double* coef = c->red + 3 * kRedBlocks;
     double* out = c->red;
     std::vector<double> hc((size_t)nrhs * kCoef, 0.0);
-    std::vector<int> stale(nrhs, 0);
+    std::vector<int> stale(nrhs, 0), anew(nrhs, 0);
     st.assign(nrhs, LState());
     // r_0 = b - A x0, rhat = r_0, u_0 = 0 (systems 0..nrhs-1 on slots 0..nrhs-1)
     const RhsSet ids = RhsSet::uniform(nrhs, 0);
@@ -1175,12 +1183,17 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
         if ((rc = reduce(nq))) return rc;
         for (int q = 0; q < nrhs; ++q) {
             if (!st[q].active) continue;
+            // Where the residuals are dependent to rounding (an operator close to the identity), the update of the
+            // largest degree that they determine, after which the system starts anew from its residual.  FP32 inner
+            // solves end there: the FP64 refinement starts them anew.
             Cd gm[kMaxL + 1];
-            if (!mr_coefficients(&c->red_host[q * kGramSlots], l, gm)) {
+            const int d = mr_coefficients(&c->red_host[q * kGramSlots], l, gm);
+            if (d == 0 || (d < l && sizeof(T) == 4)) {
                 halt(q, true);
                 continue;
             }
             st[q].omega = gm[l];
+            anew[q] = d < l;
             for (int j = 1; j <= l; ++j) {
                 hc[(size_t)q * kCoef + 2 * (j - 1)] = gm[j].real();
                 hc[(size_t)q * kCoef + 2 * (j - 1) + 1] = gm[j].imag();
@@ -1197,6 +1210,12 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
         }
         c->prof.end(c->stream);
         LS_HIP(hipGetLastError());
+        for (int q = 0; q < nrhs; ++q) {
+            if (!st[q].active || !anew[q]) continue;
+            LS_HIP(hipMemcpyAsync(rhat + q * m, R.v[0] + q * m, sizeof(cpx<T>) * m, hipMemcpyDeviceToDevice, c->stream));
+            st[q].rho0 = st[q].omega = 1.0;
+            st[q].alpha = 0.0;   // u_0 = r_0 in the next step
+        }
         first = false;
     }
     // systems whose last operation was a minimal-residual update: their residual norm
