@@ -265,7 +265,7 @@ int check_solve_buffers(const ls_ctx* c, const void* b, const void* x0, const vo
 // and precision, then per precision the right-hand sides per chunk of the x and y passes and the strided
 // passes' tile choice), in the file LS_AUTOTUNE_CACHE names, else $HOME/.cache/lsvie/autotune.txt.  A missing
 // or unreadable cache only means tuning again; a later line for the same key wins; lines of other formats
-// (an older key version) are skipped.
+// (an older key version) and those timed with other kernels are skipped.
 
 std::string autotune_path() {
     if (const char* e = std::getenv("LS_AUTOTUNE_CACHE")) return e;
@@ -273,7 +273,11 @@ std::string autotune_path() {
     return std::string(home ? home : "/tmp") + "/.cache/lsvie/autotune.txt";
 }
 
-// everything the timings depend on: device, grid, FFT lengths, batch width, layout, table kind, precision
+// Counts up with every change of the FFT passes, of the tables they read or of what a variant number stands for: a choice
+// timed with other kernels is not taken.
+constexpr int kKernelGeneration = 2;
+
+// everything the timings depend on: kernels, device, grid, FFT lengths, batch width, layout, table kind, precision
 std::string autotune_key(const Ctx* c) {
     hipDeviceProp_t prop{};
     std::string arch = "unknown";
@@ -281,8 +285,8 @@ std::string autotune_key(const Ctx* c) {
     (void)hipGetLastError();
     for (char& ch : arch)
         if (ch == ' ' || ch == ':') ch = '_';
-    return "v2:" + arch + ":cu" + std::to_string(c->num_cu) + ":n" + std::to_string(c->n1) + "x" + std::to_string(c->n2) +
-           "x" + std::to_string(c->n3) + ":L" + std::to_string(c->L1) + "x" + std::to_string(c->L2) + "x" +
+    return "v2:k" + std::to_string(kKernelGeneration) + ":" + arch + ":cu" + std::to_string(c->num_cu) + ":n" +
+           std::to_string(c->n1) + "x" + std::to_string(c->n2) + "x" + std::to_string(c->n3) + ":L" + std::to_string(c->L1) + "x" + std::to_string(c->L2) + "x" +
            std::to_string(c->L3) + ":r" + std::to_string(c->max_rhs) + ":z" + std::to_string(c->zbs) + ":h" +
            std::to_string((int)c->green_half) + ":m" + std::to_string(c->mixed);
 }
