@@ -155,9 +155,11 @@ __device__ __forceinline__ cpx<T> cdot3(cpx<T> g1, cpx<T> f1, cpx<T> g2, cpx<T> 
 // resident.  Registers set that: three components of 16 FP64 values take 192 of them, so a second wave per SIMD
 // (256) leaves 64 for everything else.  What it takes to stay within them: loads and stores through a bounds-checked
 // buffer (branches around each element kept both sides' registers alive: 160-490 spilled), scheduling fences between
-// the short DFTs, table entries requested one value ahead only, and store offsets computed again.  The table's
-// layout (green_index) gives every load of a wavefront whole lines in 16-byte pieces; entries of a k-point side by
-// side, 48 or 96 bytes per lane, or 8-byte loads cost the FP32 pass 0.12 ms at 128^3.
+// the short DFTs, table entries requested one value ahead only, and store offsets computed again.  FP64 still
+// spills 10 to 16 registers at 192 and 256, 3 to 5 at 320 and 31 at 512 with the octant table, FP32 14 to 16 at 224: two
+// waves (three) with them measured faster than one (two) without.  The table's layout (green_index) gives every load of a
+// wavefront whole lines in 16-byte pieces; entries of a k-point side by side, 48 or 96 bytes per lane, or 8-byte loads
+// cost the FP32 pass 0.12 ms at 128^3.
 // Measured before (one FP64 wave per SIMD; LDS Stockham kernels at 48 and 96) -> now, 6 right-hand sides: FP64 0.145
 // -> 0.083 ms at 48^3, 0.205 -> 0.175 at 64^3, 0.778 -> 0.59 at 96^3, 1.817 -> 1.30 at 128^3; FP32 0.109 -> 0.097 at
 // 64^3, 0.338 -> 0.305 at 96^3, 0.736 -> 0.612 at 128^3; one right-hand side at 256^3 FP64 3.72 -> 2.62, FP32 1.72 ->
