@@ -185,8 +185,8 @@ int ls_apply(ls_ctx* ctx, int i_omega, const void* u, void* Au, int n_rhs);
  * fixed 64 MiB device array that the library holds on each GPU it runs on until the process ends, instead
  * of the context's workspace.  Same arguments, result (bitwise equal to ls_apply's) and errors as ls_apply;
  * n_rhs x 3 N3 L2 L1 x 16 bytes (L_a the smallest 2^a or 3 2^a, at least 16, not below 2 N_a - 1: 50 MB for
- * one 64^3 field) must fit in the 64 MiB, else LS_ERR_ARG.  Allocates nothing and clears nothing (every value of the buffer that is read
- * was written earlier in the same call).  Every call on a GPU uses that GPU's one array, so calls that
+ * one 64^3 field) must fit in the 64 MiB, else LS_ERR_ARG.  Allocates nothing and clears nothing (every value of
+ * the buffer that is read was written earlier in the same call).  Every call on a GPU uses that GPU's one array, so calls that
  * overlap in time on one GPU (different streams or host threads) race; serialise them (contexts set up on the null
  * stream are, among themselves).  Asynchronous. */
 int ls_apply_noalloc(ls_ctx* ctx, int i_omega, const void* u, void* Au, int n_rhs);

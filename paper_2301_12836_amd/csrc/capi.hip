@@ -285,10 +285,10 @@ std::string autotune_key(const Ctx* c) {
     (void)hipGetLastError();
     for (char& ch : arch)
         if (ch == ' ' || ch == ':') ch = '_';
-    return "v2:k" + std::to_string(kKernelGeneration) + ":" + arch + ":cu" + std::to_string(c->num_cu) + ":n" +
-           std::to_string(c->n1) + "x" + std::to_string(c->n2) + "x" + std::to_string(c->n3) + ":L" + std::to_string(c->L1) + "x" + std::to_string(c->L2) + "x" +
-           std::to_string(c->L3) + ":r" + std::to_string(c->max_rhs) + ":z" + std::to_string(c->zbs) + ":h" +
-           std::to_string((int)c->green_half) + ":m" + std::to_string(c->mixed);
+    auto str = [](long long v) { return std::to_string(v); };
+    return "v2:k" + str(kKernelGeneration) + ":" + arch + ":cu" + str(c->num_cu) + ":n" + str(c->n1) + "x" + str(c->n2) + "x" +
+           str(c->n3) + ":L" + str(c->L1) + "x" + str(c->L2) + "x" + str(c->L3) + ":r" + str(c->max_rhs) + ":z" + str(c->zbs) +
+           ":h" + str(c->green_half) + ":m" + str(c->mixed);
 }
 
 bool autotune_lookup(const std::string& key, Ctx* c) {
