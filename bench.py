@@ -104,7 +104,7 @@ def apply_bytes(n, prec, nrhs):
 
 # the sources each kernel family is compiled from (a change to any of them voids its counter figures)
 FAMILY_SOURCES = {"fft_": ("common.h", "fft_core.h", "fft_reg.h", "fft_pass.h", "fft.hip", "fft_z.hip"),
-                  "contrast_": ("common.h", "fft_reg.h", "contrast.hip")}
+                  "contrast_": ("common.h", "fft_core.h", "fft_reg.h", "contrast.hip")}
 
 
 def file_hash(name):
