@@ -924,6 +924,7 @@ struct LState {
     int status = 0;          // 0 running / converged, 1 not converged, 2 breakdown, 3 non-finite
     bool active = true, done = false;
     double bnorm2 = 0, rnorm2 = 0, best = 0;
+    double anew_r2 = std::numeric_limits<double>::infinity();   // ||r||^2 when the system last started anew
     int since = 0;
     std::complex<double> rho0 = 1.0, alpha = 0.0, omega = 1.0;
 };
@@ -1184,16 +1185,19 @@ int bicgstab_l(Ctx* c, const cpx<T>* b, cpx<X>* x, const cpx<T>* ax0, cpx<T>* co
         for (int q = 0; q < nrhs; ++q) {
             if (!st[q].active) continue;
             // Where the residuals are dependent to rounding (an operator close to the identity), the update of the
-            // largest degree that they determine, after which the system starts anew from its residual.  FP32 inner
-            // solves end there: the FP64 refinement starts them anew.
+            // largest degree that they determine, after which the system starts anew from its residual, if that has
+            // halved since the last time (at most about log2(1/tol) starts).  FP32 inner solves end there: the FP64
+            // refinement starts them anew.
             Cd gm[kMaxL + 1];
-            const int d = mr_coefficients(&c->red_host[q * kGramSlots], l, gm);
-            if (d == 0 || (d < l && sizeof(T) == 4)) {
+            const double* z = &c->red_host[q * kGramSlots];
+            const int d = mr_coefficients(z, l, gm);
+            if (d == 0 || (d < l && (sizeof(T) == 4 || z[0] > 0.25 * st[q].anew_r2))) {
                 halt(q, true);
                 continue;
             }
             st[q].omega = gm[l];
             anew[q] = d < l;
+            if (anew[q]) st[q].anew_r2 = z[0];
             for (int j = 1; j <= l; ++j) {
                 hc[(size_t)q * kCoef + 2 * (j - 1)] = gm[j].real();
                 hc[(size_t)q * kCoef + 2 * (j - 1) + 1] = gm[j].imag();

@@ -27,3 +27,19 @@ def test_solves_near_the_identity(ell, rel, precision):
             assert all(i["status"] == 0 for i in infos)
             assert (res <= tol * (1 + 1e-6) + 2.0 ** -50).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("ell", [2, 4])
+@pytest.mark.parametrize("rel", [1e-5, 1e-3])
+def test_a_tolerance_below_rounding_ends(ell, rel):
+    """The solve ends (the recurred residual may fall below rounding, and the status goes by it) and leaves a field whose true
+    residual is rounding: within 2^13 unit roundoffs."""
+    m = models.random_medium((9, 6, 7), seed=4, rel=rel)
+    ctx = lsvie.context_from_model(m, omegas=[2 * np.pi * 15.0], max_rhs=2, bicgstab_l=ell)
+    b = torch.stack([ctx.rhs_moment(np.eye(6)[q], (2 + q, 2, 3)) for q in range(2)])
+    u, infos = ctx.solve(b, tol=1e-19, maxit=200, raise_on_error=False)
+    res = torch.linalg.vector_norm((b - ctx.apply(u)).reshape(2, -1), dim=1) / torch.linalg.vector_norm(b.reshape(2, -1), dim=1)
+    print(ell, rel, [(i["status"], i["iters"]) for i in infos], res.tolist(), flush=True)
+    assert all(i["iters"] <= 200 for i in infos)
+    assert (res < 2.0 ** -40).all()
+    ctx.close()
