@@ -70,7 +70,7 @@ int cover(Ctx* c) {
 int wait_for_others(Ctx* c, const Span* s, int ns) {
     for (Ctx* q : g_private) {
         StreamOrder& o = q->order;
-        if (q == c || q->device != c->device || o.n == 0 || !conflict(o.range, o.n, s, ns)) continue;
+        if (q == c || o.n == 0 || !conflict(o.range, o.n, s, ns)) continue;
         if (captured(c)) return LS_OK;
         // a stream inside a waiting call may be recording a graph: the ranges that are not covered are those of that
         // call, which its caller keeps until it returns
